@@ -43,7 +43,10 @@
  * dc_weight_radon, dc_detector_bp_adjoint and dc_cone_bp_adjoint use for their
  * fixed-point scales, and one volume-sized float32 buffer per sample into which
  * dc_cone_bp_adjoint rewrites the (ReLU-masked) gradient in z-bricks of 16
- * voxels (nz rounded up to a multiple of 16); stage calls on one plan
+ * voxels (nz rounded up to a multiple of 16), and a workspace of at most 512 MiB into
+ * which dc_weight_radon (and its _noalloc form) and dc_detector_bp_adjoint rewrite their
+ * views, a batch at a time, where bins are as wide as pixels to twice as wide (without it,
+ * if it cannot be allocated, they run another form); stage calls on one plan
  * must therefore be ordered on one stream (use one plan per concurrent stream).  Plans must be created before any stream
  * capture that uses them; stage calls enqueue kernels only (no memset, no
  * allocation), so they can be captured into a graph.
@@ -127,7 +130,8 @@ dc_status dc_plan_destroy(dc_plan plan);
  * that of the cone BP only where one block's detector footprint is too large to
  * stage in LDS and its taps take the direct form.
  *   splat_angles   sinogram rows one weighted-Radon / detector-Radon workgroup holds
- *                  in LDS, 1..8 (0 on input: as many as fit 80 KiB);
+ *                  in LDS, 1..8 (0 on input: as many as fit 80 KiB), where bins are
+ *                  narrower than pixels or more than twice as wide (no effect otherwise);
  *   interp_tile_u  detector-BP pixel tile width, 32 or 64 (tile height 64);
  *   interp_angles  detector-BP angles staged per chunk, 16, 32 or 64;
  *   bp_block_y     cone-BP voxel block rows, 16 or 32 (block 16 x rows x 8);
@@ -171,7 +175,8 @@ dc_status dc_plan_autotune(dc_plan plan, uint32_t flags, hipStream_t stream, dc_
  * dc_plan_create, for a one-scan plan.  They decide the safety and accuracy of
  * the fixed-point stages (dc_weight_radon and dc_detector_bp_adjoint accumulate
  * pixel terms per (angle, bin); dc_cone_bp_adjoint voxel terms per detector cell):
- * each term is rounded to an integer number of units, the largest term of a view
+ * each term (dc_detector_bp_adjoint into float32: each pixel, its two hat weights then
+ * summed in float32) is rounded to an integer number of units, the largest term of a view
  * (splat: max |w_cos g| or |GgF| over the view's pixels) or of the call (cone FP:
  * max |Gf| times the view's bound on (D/U)^2) taking qmax units, and a sum of at
  * most max_terms such integers never leaves 32 bits.  So every output's absolute
@@ -210,7 +215,8 @@ dc_status dc_weight_radon(dc_plan plan, const float* g, void* R, dc_dtype tR,
  * serving loops, harnesses that forbid allocation): the same stage, bit for bit,
  * with its per-view fixed-point scale words in a static device array of 65536
  * words (256 KiB) that each GPU holds until the process ends, instead of the
- * plan's scratch.  Nothing is allocated in the call.  At most 65536 views per
+ * plan's scratch (the views are rewritten into the plan's workspace in both).  Nothing
+ * is allocated in the call.  At most 65536 views per
  * call (DC_ESHAPE beyond).  Every call on one GPU shares that GPU's array:
  * calls that overlap in time on one GPU (other streams, other plans, other
  * threads) race and must be ordered by the caller.  The array is cleared by a

@@ -75,6 +75,17 @@ static dc_status build_plan(const dc_grid* g, const dc_view* views, int32_t n, c
                                                ((g->nz + kConeBrick - 1) / kConeBrick * kConeBrick) * sizeof(float))) !=
           hipSuccess)
     return fail(e == hipErrorOutOfMemory ? DC_ENOMEM : DC_EHIP, std::string("plan scratch: ") + hipGetErrorString(e));
+  // the splat's workspace; without it (no memory left, or a geometry outside its rule)
+  // the atomic form runs
+  if (p->shear_g > 0) {
+    const size_t bytes = splat_shear_workspace(*p);
+    if (hipMalloc((void**)&p->d_splat_ws, bytes) == hipSuccess) {
+      p->splat_ws_bytes = bytes;
+    } else {
+      p->d_splat_ws = nullptr;
+      (void)hipGetLastError();
+    }
+  }
   return DC_OK;
 }
 
@@ -86,16 +97,18 @@ static dc_status upload_tables(Plan* p, const dc_view* views, const KernelShape&
   const dc_status st = plan_tables(g, views, n, p->first.data(), n_samples, ks, &hp, &err);
   if (st != DC_OK) return fail(st, err);
   // upload into new buffers; the plan keeps its old tables unless all succeed
-  enum { kAng, kTrig, kView, kFrame, kProj, kRmax2, kChunks, kFirst, kForm, kN };
+  enum { kAng, kTrig, kView, kFrame, kProj, kRmax2, kChunks, kFirst, kForm, kShearGr, kShearRow, kN };
   void* fresh[kN] = {};
   const std::vector<int> forms(hp.cone_form.begin(), hp.cone_form.end());
   const void* src[kN] = {hp.ang.data(), hp.trig.data(), hp.vf.data(), hp.frame.data(),
-                         hp.proj.data(), hp.rmax2.data(), hp.chunks.data(), p->first.data(), forms.data()};
+                         hp.proj.data(), hp.rmax2.data(), hp.chunks.data(), p->first.data(), forms.data(),
+                         hp.shear_groups.data(), hp.shear_rows.data()};
   const size_t bytes[kN] = {hp.ang.size() * sizeof(double), hp.trig.size() * sizeof(float),
                             hp.vf.size() * sizeof(float), hp.frame.size() * sizeof(double),
                             hp.proj.size() * sizeof(double), hp.rmax2.size() * sizeof(float),
                             hp.chunks.size() * sizeof(int), p->first.size() * sizeof(int),
-                            forms.size() * sizeof(int)};
+                            forms.size() * sizeof(int), hp.shear_groups.size() * sizeof(ShearGroup),
+                            hp.shear_rows.size() * sizeof(ShearRow)};
   hipError_t e = hipSuccess;
   for (int i = 0; i < kN && e == hipSuccess; ++i) {
     e = hipMalloc(&fresh[i], bytes[i]);
@@ -108,7 +121,7 @@ static dc_status upload_tables(Plan* p, const dc_view* views, const KernelShape&
   }
   // the old tables may still be read by queued kernels: let the device drain first
   void* old[kN] = {p->d_ang, p->d_trig, p->d_view, p->d_frame, p->d_proj, p->d_rmax2, p->d_chunks, p->d_first,
-                   p->d_form};
+                   p->d_form, p->d_shear_groups, p->d_shear_rows};
   bool any_old = false;
   for (void* q : old) any_old = any_old || q;
   if (any_old) {
@@ -125,6 +138,12 @@ static dc_status upload_tables(Plan* p, const dc_view* views, const KernelShape&
   p->d_chunks = (int4*)fresh[kChunks];
   p->d_first = (int*)fresh[kFirst];
   p->d_form = (int*)fresh[kForm];
+  p->d_shear_groups = (ShearGroup*)fresh[kShearGr];
+  p->d_shear_rows = (ShearRow*)fresh[kShearRow];
+  p->shear_g = hp.shear_g;
+  p->shear_groups = (int)hp.shear_groups.size();
+  p->shear_pad_rows[0] = hp.shear_pad_rows[0];
+  p->shear_pad_rows[1] = hp.shear_pad_rows[1];
   p->shape = ks;
   p->shape.splat_kc = hp.splat_kc;
   p->interp_wl = hp.interp_wl;
@@ -143,7 +162,8 @@ static dc_status upload_tables(Plan* p, const dc_view* views, const KernelShape&
 
 static void free_plan(Plan* p) {
   void* ptrs[] = {p->d_ang,    p->d_trig,  p->d_view,    p->d_frame,  p->d_proj,   p->d_rmax2,
-                  p->d_chunks, p->d_first, p->d_form,    p->d_scratch, p->d_masked};
+                  p->d_chunks, p->d_first, p->d_form,    p->d_scratch, p->d_masked, p->d_shear_groups,
+                  p->d_shear_rows, p->d_splat_ws};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   delete p;

@@ -98,6 +98,13 @@ struct Plan {
   int n_chunks = 0;
   int splat_kc = 0;              // max angles per chunk
   int splat_max_terms = 0;       // max pixels that share one (angle, bin)
+  // the splat's gather form (splat_shear.hip): its tables and the workspace of rewritten
+  // views (null: the atomic form runs)
+  ShearGroup* d_shear_groups = nullptr;
+  ShearRow* d_shear_rows = nullptr;
+  int shear_g = 0, shear_groups = 0, shear_pad_rows[2] = {0, 0};
+  float* d_splat_ws = nullptr;
+  size_t splat_ws_bytes = 0;
   int splat_checked = 1;         // 0 when every pixel lands on bins [-1, n_s) for all angles
   int interp_wl = 0;             // LDS window length for the interpolating kernels
                                  // (above kInterpLocalAbove: the fixed-point position tap form)
@@ -172,6 +179,11 @@ hipError_t launch_zero_u32(unsigned* p, int n, hipStream_t s);
 // (nullptr: the plan's scratch)
 hipError_t launch_splat(const Plan& p, const void* img, dc_dtype t_in, bool wcos, float scale,
                         void* out, dc_dtype t_out, int v0, int nv, hipStream_t s, unsigned* vmax_words = nullptr);
+// the same stage in its gather form, for plans whose geometry takes it (p.d_splat_ws);
+// vmax: the nv views' largest magnitudes (float bits)
+hipError_t launch_splat_shear(const Plan& p, const void* img, dc_dtype t_in, bool wcos, float scale, void* out,
+                              dc_dtype t_out, int v0, int nv, bool exact, hipStream_t s, const unsigned* vmax);
+size_t splat_shear_workspace(const Plan& p);
 // The allocation-free splat's static scratch (radon2d.hip): kNoAllocViews words per
 // GPU; *out = its address on `device`, which must be current (looked up once per device).
 static constexpr int kNoAllocViews = 65536;

@@ -117,6 +117,182 @@ dc_status check_shape(const KernelShape& ks, std::string* err) {
   return DC_OK;
 }
 
+// The angle group's common slope: the middle of its angles' beta / alpha
+static double shear_slope(const HostPlan& p, int k0, int kn, int col) {
+  double lo = 1e300, hi = -1e300;
+  for (int k = k0; k < k0 + kn; ++k) {
+    const double slope = p.ang[3 * k + 1 - col] / p.ang[3 * k + col];
+    lo = std::min(lo, slope);
+    hi = std::max(hi, slope);
+  }
+  return 0.5 * (lo + hi);
+}
+
+// One angle group's tables for blocks of B rows: false when some set of rows leaves one bin
+// on some angle.
+static bool shear_group(const dc_grid* g, const HostPlan& p, int k0, int kn, int col, int B, ShearGroup* out,
+                        std::vector<ShearRow>* rows) {
+  ShearGroup gr{};
+  gr.k0 = k0;
+  gr.kn = kn;
+  gr.col = col;
+  const int n = col ? g->nv : g->nu, walk = col ? g->nu : g->nv;
+  gr.rows = B;
+  gr.blocks = (walk + B - 1) / B;
+  const double slope = shear_slope(p, k0, kn, col), wc = 0.5 * (B - 1);
+  auto sigma = [&](int w) { return (w * slope + 6755399441055744.0) - 6755399441055744.0; };   // rounded (1.5 2^52)
+  // the rows below and above rho = 0, each in order; an odd count gives its row nearest
+  // to 0 to the other set
+  int order[kShearPad], above[kShearPad], n0 = 0, n1 = 0;
+  for (int w = 0; w < B; ++w) {
+    if (w * slope - sigma(w) >= 0.0) above[n1++] = w;
+    else order[n0++] = w;
+  }
+  if (n0 % 2) {
+    int best = 0;
+    for (int i = 1; i < n0; ++i)
+      if (order[i] * slope - sigma(order[i]) > order[best] * slope - sigma(order[best])) best = i;
+    above[n1++] = order[best];
+    for (int i = best; i + 1 < n0; ++i) order[i] = order[i + 1];
+    --n0;
+  }
+  for (int i = 0; i < n1; ++i) order[n0 + i] = above[i];
+  gr.n_first = n0;
+  gr.shift = (int)sigma(B - 1);
+  const int pitch = n + kShearPad;
+  auto offset = [&](int i) {
+    const int w = order[std::min(i, B - 1)];
+    return (int)((w * (long long)pitch - (long long)sigma(w)) * 16);
+  };
+  for (int i = 0; i < kShearAhead; ++i) gr.first[i] = offset(i);
+  double lo[2][4], hi[2][4];
+  for (auto* a : {&lo, &hi})
+    for (auto& r : *a)
+      for (double& v : r) v = a == &lo ? 1e300 : -1e300;
+  unsigned step[4];
+  for (int q = 0; q < 4; ++q) {
+    const int k = k0 + std::min(q, kn - 1);   // a short group repeats its last angle
+    const double al = p.ang[3 * k + col], be = p.ang[3 * k + 1 - col], de = be - slope * al;
+    gr.alpha[q] = (float)al;
+    gr.delta[q] = (float)de;
+    gr.a[q] = al;
+    gr.b[q] = be;
+    gr.base[q] = p.ang[3 * k + 2] + wc * de;
+    // low word of the walk's step as k_splat rounds it; multiples of it keep their low words
+    step[q] = (unsigned)(unsigned long long)std::llrint(be * 4294967296.0);
+    gr.block_step[q] = (unsigned)B * step[q];
+  }
+  ShearRow list[kShearPad] = {};
+  for (int i = 0; i < B; ++i) {
+    const int w = order[i], s = i < gr.n_first ? 0 : 1;
+    ShearRow& r = list[i];
+    r.ahead = offset(i + kShearAhead);
+    r.rho = (float)(w * slope - sigma(w));
+    r.wc = (float)(w - wc);
+    r.sigma = (int)sigma(w);
+    for (int q = 0; q < 4; ++q) {
+      const double al = gr.a[q], de = gr.b[q] - slope * al;
+      const double rest = al * (w * slope - sigma(w)) + (w - wc) * de;
+      r.rest[q] = (float)rest;
+      r.step[q] = (unsigned)w * step[q];
+      lo[s][q] = std::min(lo[s][q], rest);
+      hi[s][q] = std::max(hi[s][q], rest);
+    }
+  }
+  for (int s = 0; s < 2; ++s)
+    for (int q = 0; q < 4; ++q) {
+      if (hi[s][q] - lo[s][q] > 1.0 - 1e-5) return false;
+      gr.lo[s][q] = hi[s][q] < lo[s][q] ? 0.f : (float)lo[s][q];
+    }
+  *out = gr;
+  rows->insert(rows->end(), list, list + kShearPad);
+  return true;
+}
+
+// Tables of the splat's gather form.  On every angle the larger of |A|, |B| (alpha) must lie
+// in [1/2, 1].  A set's rho spans 1/2 at most, so its positions stay within one bin where
+// alpha / 2 + (B - 1) |delta| does.  Of the angle group sizes 4, 2, 1 and the block heights B
+// below that bound, the pair with the least work per angle: 12 + 5 G operations per row and
+// about 13 per view, angle and set at the end of each block (4 views).  4 angles and 32 rows on
+// the 512^2 detector at n_theta = 360.
+static void shear_tables(const dc_grid* g, HostPlan* p) {
+  const int K = g->n_theta;
+  p->shear_g = 0;
+  auto is_col = [&](int k) { return std::fabs(p->ang[3 * k + 1]) > std::fabs(p->ang[3 * k]) ? 1 : 0; };
+  for (int k = 0; k < K; ++k) {
+    const double al = std::fabs(p->ang[3 * k + is_col(k)]);
+    if (!(al >= 0.5 && al <= 1.0 + 1e-9)) return;
+  }
+  // byte offsets within a view group stay in 32 bits
+  if ((double)(g->nu + kShearPad) * (g->nv + kShearPad) * 32.0 > 2147483647.0) return;
+  auto group_end = [&](int k, int G) {
+    int e = k;
+    while (e < K && e - k < G && is_col(e) == is_col(k)) ++e;
+    return e;
+  };
+  struct Choice {
+    double cost;
+    int G, B[2];
+  };
+  std::vector<Choice> choices;
+  for (int G : {4, 2, 1}) {
+    // sinogram rows of four views and the fractions of one line per angle, in one workgroup's LDS
+    if ((long long)G * 4 * (4 * shear_row_words(g->n_s) + std::max(g->nu, g->nv) + 2 * kShearPad) + 1024 > kLdsPerWorkgroup)
+      continue;
+    double most[2] = {kShearPad, kShearPad};
+    for (int k = 0; k < K; k = group_end(k, G)) {
+      const int e = group_end(k, G), col = is_col(k);
+      const double slope = shear_slope(*p, k, e - k, col);
+      for (int q = k; q < e; ++q) {
+        const double al = p->ang[3 * q + col], de = std::fabs(p->ang[3 * q + 1 - col] - slope * al);
+        if ((most[col] - 1.0) * de > 1.0 - 1e-5 - 0.5 * std::fabs(al)) most[col] = (1.0 - 1e-5 - 0.5 * std::fabs(al)) / de + 1.0;
+      }
+    }
+    Choice c{0.0, G, {0, 0}};
+    for (int col = 0; col < 2; ++col) {
+      const int walk = col ? g->nu : g->nv;
+      double least = 1e300;
+      for (int b = (int)most[col] & ~1; b >= 2; b -= 2) {
+        const double cost = (walk + b - 1) / b * (b * (12.0 + 5.0 * G) + 2.0 * 13.0 * 4.0 * G) / G;
+        if (cost >= least) continue;
+        least = cost;
+        c.B[col] = b;
+      }
+      c.cost += least;
+    }
+    if (c.cost < 1e299) choices.push_back(c);
+  }
+  std::sort(choices.begin(), choices.end(), [](const Choice& a, const Choice& b) { return a.cost < b.cost; });
+  for (Choice& c : choices) {
+    std::vector<ShearGroup> groups;
+    std::vector<ShearRow> rows;
+    int k = 0;
+    while (k < K) {
+      const int e = group_end(k, c.G), col = is_col(k);
+      ShearGroup gr;
+      if (shear_group(g, *p, k, e - k, col, c.B[col], &gr, &rows)) {
+        groups.push_back(gr);
+        k = e;
+        continue;
+      }
+      // an odd row that changed sets leaves the bin: lower blocks, from the start
+      if ((c.B[col] -= 2) < 2) break;
+      groups.clear();
+      rows.clear();
+      k = 0;
+    }
+    if (k < K) continue;
+    p->shear_g = c.G;
+    p->shear_groups = std::move(groups);
+    p->shear_rows = std::move(rows);
+    for (int col = 0; col < 2; ++col) {
+      const int walk = col ? g->nu : g->nv;
+      p->shear_pad_rows[col] = (walk + c.B[col] - 1) / c.B[col] * c.B[col];
+    }
+    return;
+  }
+}
+
 dc_status plan_tables(const dc_grid* g, const dc_view* views, int n, const int* first, int n_samples,
                       const KernelShape& ks, HostPlan* p, std::string* err) {
   {
@@ -191,6 +367,8 @@ dc_status plan_tables(const dc_grid* g, const dc_view* views, int n, const int* 
     kk = e;
   }
   p->n_chunks = (int)p->chunks.size() / 4;
+
+  shear_tables(g, p);
 
   p->vf.assign(4 * n, 0.f);
   p->rmax2.assign(n, 0.f);

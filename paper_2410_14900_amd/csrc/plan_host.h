@@ -55,6 +55,41 @@ inline float fixed_point_qmax(int max_terms) {
   return q < 2097152.0 ? (float)q : 2097152.0f;
 }
 
+// The gather form of the splat (splat_shear.hip).
+static constexpr int kShearPad = 64;     // zero pixels around the rows of its copy; at most that many rows per block
+static constexpr int kShearAhead = 2;    // rows loaded ahead of their use
+// A group of up to four consecutive angles that share their shifts.  Row w of a block of
+// `rows` rows is shifted by sigma(w) = rint(w slope) pixels along the fast axis, which
+// leaves  w beta - sigma alpha = alpha rho + (w - wc) delta + wc delta  bins on an angle,
+// rho = w slope - sigma in [-1/2, 1/2], delta = beta - slope alpha, wc the block's middle.
+// The rows are taken in two sets, rho below and above 0, over each of which the part that
+// varies, rest = alpha rho + (w - wc) delta, stays within one bin on every angle.
+struct ShearGroup {
+  int k0, kn, col;          // first angle, count, 1: walks the image by columns
+  int rows, blocks;         // rows per block (even), blocks per image
+  int n_first;              // rows of the first set (even)
+  int shift;                // sigma of a block's last row
+  int first[kShearAhead];   // byte offsets (as ShearRow::ahead) of the first rows taken
+  unsigned block_step[4];   // low words of rows x beta in 32.32 fixed point
+  int pad;
+  float lo[2][4];           // smallest rest of each set and angle
+  float alpha[4], delta[4];
+  double a[4], b[4];        // alpha, beta
+  double base[4];           // C + wc delta: t of column 0 of a block at row 0, without the rest
+};
+struct ShearRow {           // one row of a block, in the order taken
+  int ahead;                // (w pitch - sigma) records of 16 bytes, in bytes, of the row kShearAhead further on
+  float rho, wc;            // rho, w - wc
+  int sigma;
+  float rest[4];
+  unsigned step[4];         // low words of w beta in 32.32 fixed point
+  int pad[4];
+};
+// words between the sinogram rows a workgroup holds in LDS: kShearGuard guard words at each
+// end, and 16 more than a multiple of 64, so the rows of its four views start 16 banks apart
+static constexpr int kShearGuard = 3;
+inline int shear_row_words(int n_s) { return (n_s + 2 * kShearGuard + 47) / 64 * 64 + 16; }
+
 struct HostPlan {
   // per angle k: A_k = du cos mu/ds, B_k = dv sin mu/ds, C_k = fractional bin of pixel (0,0)
   std::vector<double> ang;       // [n_theta][3]
@@ -70,6 +105,11 @@ struct HostPlan {
   int splat_kc = 0;              // angles per splat workgroup
   int splat_max_terms = 0;       // bound on pixels sharing one (angle, bin)
   int splat_checked = 1;         // 1: some pixel may land outside bins [-1, n_s)
+  // the gather form of the splat: angles per group, 4, 2 or 1 (0: the geometry does not take it)
+  int shear_g = 0;
+  std::vector<ShearGroup> shear_groups;
+  std::vector<ShearRow> shear_rows;       // [groups][kShearPad]
+  int shear_pad_rows[2] = {0, 0};         // rows of the copy's row and column forms (blocks x rows)
   int interp_wl = 0;             // detector-BP window length
   int cone_max_terms = 0;        // bound on voxel centres per detector cell in one view
   int bp_stage = 0;              // staged rows per cone-BP thread and view (0: direct taps)

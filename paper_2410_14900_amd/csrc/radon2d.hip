@@ -444,6 +444,11 @@ hipError_t launch_splat(const Plan& p, const void* img, dc_dtype t_in, bool wcos
 #undef DC_ABSMAX
     hipError_t e2 = hipGetLastError();
     if (e2 != hipSuccess) return e2;
+    // The gather forms where the geometry takes them (6.3 and 3.9 ms against 10.6 for 496 views of
+    // 512^2 at 360 angles): float32 sums for the detector Radon stored in float32, this form's own
+    // integer terms otherwise, so that R and whatever is stored in 16 bits is the same in both.
+    if (p.d_splat_ws)
+      return launch_splat_shear(p, img, t_in, wcos, scale, out, t_out, v0, nv, wcos || t_out != DC_F32, s, vmax);
     return by_dtype(t_out, [&](auto tout) {
       using Tout = decltype(tout);
 #define DC_SPLAT(W, C)                                                                                         \
