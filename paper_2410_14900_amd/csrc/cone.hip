@@ -95,6 +95,33 @@ __device__ __forceinline__ ColumnMapZ column_map_z(const double* __restrict__ P,
   return c;
 }
 
+// The backprojection's column, with every rounding spelled out: its forms (one or several
+// threads per column segment) give the same bits whatever the compiler fuses.  v at the
+// second voxel takes its step unrounded.
+struct ColumnMapZB : ColumnMapZ {
+  float w1;         // v - jv0 - 1/2 at the second voxel of the segment
+};
+
+__device__ __forceinline__ ColumnMapZB column_map_z_bp(const double* __restrict__ P, int ix, int iy, int iz0) {
+#pragma clang fp contract(off)
+  const double den = fma((double)ix, P[0], fma((double)iy, P[1], P[3]));
+  const double nu = fma((double)ix, P[4], fma((double)iy, P[5], P[7]));
+  const double nv = fma((double)ix, P[8], fma((double)iy, P[9], fma((double)iz0, P[10], P[11])));
+  const float rden = __builtin_amdgcn_rcpf((float)den);
+  const int iu0 = (int)floorf((float)nu * rden), jv0 = (int)floorf((float)nv * rden);
+  const float nu0 = (float)fma(-(double)iu0, den, nu), nv0 = (float)fma(-(double)jv0, den, nv), dv = (float)P[10];
+  const float yu = fmaf(nu0, rden, -0.5f) + kRoundMagic;
+  ColumnMapZB c;
+  c.fu = nu0 * rden - (yu - kRoundMagic);
+  c.i = iu0 + (int)(__float_as_uint(yu) - kRoundMagicBits);
+  c.jv0 = jv0;
+  c.r2 = rden * rden;
+  c.w0m = fmaf(nv0, rden, -0.5f);
+  c.w1 = fmaf(dv, rden, c.w0m);
+  c.dw = dv * rden;
+  return c;
+}
+
 // Column set-up of the cone adjoint's general forms.  The numerators are taken
 // about iu0 + 1/2 and jv0 + 1/2 (any integers within a pixel of the projection:
 // the hardware reciprocal serves), so n rr = u - iu0 - 1/2 and likewise v, and
@@ -163,6 +190,8 @@ struct Box {
   int i_lo, j_lo, w, h;
 };
 
+// EACH: every eight lanes their own view's (P differs between them).
+template <bool EACH = false>
 __device__ __forceinline__ Box block_footprint(const double* __restrict__ P, int bx0, int bx1, int by0, int by1,
                                                int bz0, int bz1) {
   const int lane = threadIdx.x & 63;
@@ -182,10 +211,16 @@ __device__ __forceinline__ Box block_footprint(const double* __restrict__ P, int
     jmin = fminf(jmin, __shfl_xor(jmin, m, 8));
     jmax = fmaxf(jmax, __shfl_xor(jmax, m, 8));
   }
-  imin = fmaxf(__shfl(imin, 0), -1.0e6f);
-  imax = fminf(__shfl(imax, 0), 1.0e6f);
-  jmin = fmaxf(__shfl(jmin, 0), -1.0e6f);
-  jmax = fminf(__shfl(jmax, 0), 1.0e6f);
+  if (!EACH) {
+    imin = __shfl(imin, 0);
+    imax = __shfl(imax, 0);
+    jmin = __shfl(jmin, 0);
+    jmax = __shfl(jmax, 0);
+  }
+  imin = fmaxf(imin, -1.0e6f);
+  imax = fminf(imax, 1.0e6f);
+  jmin = fmaxf(jmin, -1.0e6f);
+  jmax = fminf(jmax, 1.0e6f);
   Box b;
   b.i_lo = (int)floorf(imin) - 1;
   b.j_lo = (int)floorf(jmin) - 1;
@@ -208,8 +243,13 @@ inline constexpr bool kBpSixWaves = (FORM == kConeQuadratic || FORM == kConeGene
 // (staged form only) is the plan's choice for the sample (ConeForm), or
 // kConeMixed: a launch over samples of different forms reads each workgroup's
 // form from `forms` (one entry per sample).
-template <typename T, int STAGE, int PITCH, int FORM, int BY>
-__global__ __launch_bounds__(kBX * BY) __attribute__((amdgpu_waves_per_eu(kBpSixWaves<STAGE, FORM> ? 6 : 1)))
+// ZP > 1 is the form for small volumes, whose blocks would leave most CUs idle: the block is
+// kBX x BY / ZP x kZC, each of its column segments is shared by ZP threads (every one sets
+// the column up and takes kZC / ZP of its voxels, the arithmetic of each unchanged), and
+// footprints are fetched two views ahead, since a view's few voxels no longer cover one
+// fetch.
+template <typename T, int STAGE, int PITCH, int FORM, int BY, int ZP>
+__global__ __launch_bounds__(kBX * BY) __attribute__((amdgpu_waves_per_eu(ZP == 1 && kBpSixWaves<STAGE, FORM> ? 6 : 1)))
 void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
                                                  const double* __restrict__ proj, int acc_in, int relu, int v0,
                                                  int nv, const int* __restrict__ first, int s_lo, int nzb,
@@ -231,36 +271,40 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
     nv = max(0, ve - vb);
   }
   f += (size_t)smp * g.nx * g.ny * g.nz;
-  const int bx0 = blockIdx.x * kBX, by0 = blockIdx.y * BY, bz0 = zb * kZC;
-  const int bx1 = min(g.nx, bx0 + kBX) - 1, by1 = min(g.ny, by0 + BY) - 1, bz1 = min(g.nz, bz0 + kZC) - 1;
-  const int ix = bx0 + threadIdx.x, iy = by0 + threadIdx.y, iz0 = bz0;
-  float acc[kZC];
+  constexpr int kBY = BY / ZP, kZ = kZC / ZP;   // block rows; voxels per thread, from zs on
+  const int bx0 = blockIdx.x * kBX, by0 = blockIdx.y * kBY, bz0 = zb * kZC;
+  const int bx1 = min(g.nx, bx0 + kBX) - 1, by1 = min(g.ny, by0 + kBY) - 1, bz1 = min(g.nz, bz0 + kZC) - 1;
+  const int zs = ZP == 1 ? 0 : (int)threadIdx.y / kBY * kZ;
+  const int ix = bx0 + threadIdx.x, iy = by0 + (ZP == 1 ? threadIdx.y : threadIdx.y % kBY), iz0 = bz0;
+  float acc[kZ];
 #pragma unroll
-  for (int z = 0; z < kZC; ++z) acc[z] = 0.f;
+  for (int z = 0; z < kZ; ++z) acc[z] = 0.f;
   const size_t npix = (size_t)g.nu * g.nv;
   if constexpr (STAGE == 0) {
     for (int v = v0; v < v0 + nv; ++v) {
       const ColumnMap c = column_map(proj + 12 * v, ix, iy, iz0);
       const T* img = gF + (size_t)v * npix;
 #pragma unroll
-      for (int z = 0; z < kZC; ++z) {
+      for (int u = 0; u < kZ; ++u) {
+        const int z = zs + u;
         const float den = z == 0 ? c.den : fmaf((float)z, c.dden, c.den);
         const float r = __builtin_amdgcn_rcpf(den);
-        const float u = (z == 0 ? c.lu : fmaf((float)z, c.ldu, c.lu)) * r;
-        const float w = (z == 0 ? c.lv : fmaf((float)z, c.ldv, c.lv)) * r;
-        const float fu0 = floorf(u), fw0 = floorf(w);
-        const float fu = u - fu0, fw = w - fw0;
+        const float pu = (z == 0 ? c.lu : fmaf((float)z, c.ldu, c.lu)) * r;
+        const float pw = (z == 0 ? c.lv : fmaf((float)z, c.ldv, c.lv)) * r;
+        const float fu0 = floorf(pu), fw0 = floorf(pw);
+        const float fu = pu - fu0, fw = pw - fw0;
         const int i = c.iu0 + (int)fu0, j = c.jv0 + (int)fw0;
         const float a00 = tap(img, i, j, g.nu, g.nv), a01 = tap(img, i + 1, j, g.nu, g.nv);
         const float a10 = tap(img, i, j + 1, g.nu, g.nv), a11 = tap(img, i + 1, j + 1, g.nu, g.nv);
         const float top = fmaf(fu, a01 - a00, a00), bot = fmaf(fu, a11 - a10, a10);
-        acc[z] = fmaf(r * r, fmaf(fw, bot - top, top), acc[z]);
+        acc[u] = fmaf(r * r, fmaf(fw, bot - top, top), acc[u]);
       }
     }
   } else {
     // raw storage values: converted to float32 only when written to LDS, so
     // no use of a load comes before the interpolation of the current view
-    T stg[STAGE > 0 ? STAGE : 1];
+    constexpr int kDepth = ZP == 1 ? 1 : 2;   // views fetched ahead
+    T stg[kDepth][STAGE > 0 ? STAGE : 1];
     // fetch view v's footprint into registers: staged row r of the box (detector
     // row j_lo + r) sits at tile[r * kLP + c], and PITCH / 64 whole waves stage
     // one row, kBPThreads / PITCH rows per pass, so a wave's row is uniform and
@@ -274,61 +318,113 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
     constexpr int kRowsPerPass = STAGE > 0 ? kBPThreads / PITCH : 1;
     const int scol = tid & (PITCH - 1);
     const int srow = __builtin_amdgcn_readfirstlane(tid / PITCH);
-    auto load_stage = [&](int v, const Box& b) {
+    auto load_stage = [&](int v, const Box& b, T (&stg)[STAGE]) {
       const __amdgpu_buffer_rsrc_t im =
           __builtin_amdgcn_make_buffer_rsrc((void*)(gF + (size_t)v * npix), (short)0, (int)img_bytes, kBufferWord3);
       const int i_lo = __builtin_amdgcn_readfirstlane(b.i_lo), j_lo = __builtin_amdgcn_readfirstlane(b.j_lo);
       const bool in = (unsigned)(i_lo + scol) < (unsigned)g.nu;
       const unsigned cb = (unsigned)scol * (unsigned)sizeof(T);
+      const unsigned past = in ? 0u : 0x80000000u;
 #pragma unroll
       for (int s = 0; s < STAGE; ++s) {
         const int jj = j_lo + srow + s * kRowsPerPass;
         const unsigned off = (unsigned)(jj * g.nu + i_lo) * (unsigned)sizeof(T) + cb;
-        buffer_load_raw(im, in ? off : img_bytes, stg[s]);
+        if constexpr (ZP == 1) buffer_load_raw(im, in ? off : img_bytes, stg[s]);
+        else buffer_load_raw(im, off | past, stg[s]);
       }
     };
     // element s of thread tid is staged row srow + s kRowsPerPass, column scol.
     // Nothing reads this buffer until the barrier that ends the current view
-    auto store_stage = [&](int buf) {
+    auto store_stage = [&](int buf, const T (&stg)[STAGE]) {
 #pragma unroll
       for (int s = 0; s < STAGE; ++s) tile[buf][(srow + s * kRowsPerPass) * kLP + scol] = to_f32(stg[s]);
     };
-    // Footprints are computed by one wave per view, two views ahead, and passed
+    // ZP == 1: footprints are computed by one wave per view, two views ahead, and passed
     // on in a two-slot LDS ring: the box of view v sits in slot (v - v0) & 1 from
     // the barrier that ends iteration v - 2 until all threads have read it at the
     // start of iteration v - 1, after which the slot takes the box of view v + 2.
-    __shared__ int4 sBox[2];
+    // ZP > 1: footprints and projection matrices are set out for 64 views at a time, by all
+    // waves, 64 views ahead (a wave's chain of shuffles would hold up every view's barrier).
+    constexpr int kAhead = 64, kRing = ZP == 1 ? 2 : 2 * kAhead;
+    __shared__ int4 sBox[kRing];
+    __shared__ double sP[ZP == 1 ? 1 : kRing][12];
     const int wave = tid >> 6;
     auto publish = [&](int v, int slot) {
       const Box b = block_footprint(proj + 12 * v, bx0, bx1, by0, by1, bz0, bz1);
       if ((tid & 63) == 0) sBox[slot] = make_int4(b.i_lo, b.j_lo, b.w, b.h);
     };
-    auto box_of = [&](int slot) {
-      const int4 b = sBox[slot];
+    auto set_out = [&](int k0) {   // views v0 + k0 .. + 63
+      for (int q = tid; q < kAhead * 12; q += kBPThreads) {
+        const int k = k0 + q / 12;
+        if (k < nv) sP[k & (kRing - 1)][q % 12] = proj[12 * (v0 + k) + q % 12];
+      }
+      const int k = k0 + tid / 8;
+      const Box b = block_footprint<true>(proj + 12 * (v0 + min(k, nv - 1)), bx0, bx1, by0, by1, bz0, bz1);
+      if (k < nv && (tid & 7) == 0) sBox[k & (kRing - 1)] = make_int4(b.i_lo, b.j_lo, b.w, b.h);
+    };
+    static_assert(ZP == 1 || kBPThreads == 8 * kAhead, "eight lanes per view");
+    auto box_of = [&](int k) {
+      const int4 b = sBox[k & (kRing - 1)];
       return Box{b.x, b.y, b.z, b.w};
     };
-    Box cur{0, 0, 0, 0};
+    Box cur{0, 0, 0, 0}, nx1{0, 0, 0, 0};   // boxes of this view and, ZP > 1, the next
     if (nv > 0) {
-      if (wave < 2 && wave < nv) publish(v0 + wave, wave);
+      if constexpr (ZP == 1) {
+        if (wave < 2 && wave < nv) publish(v0 + wave, wave);
+      } else {
+        set_out(0);
+      }
       __syncthreads();
       cur = box_of(0);
-      load_stage(v0, cur);
-      store_stage(0);
+      load_stage(v0, cur, stg[0]);
+      store_stage(0, stg[0]);
+      if (kDepth == 2) {
+        nx1 = box_of(min(1, nv - 1));
+        load_stage(min(v0 + 1, v0 + nv - 1), nx1, stg[1 % kDepth]);
+      }
     }
     __syncthreads();
     // the view loop for one form F (kConeMixed takes the sample's form at run time:
     // one uniform branch per workgroup, the same arithmetic as the form's own kernel)
     auto view_loop = [&](auto form_tag) __attribute__((always_inline)) {
     constexpr int F = decltype(form_tag)::value;
-    for (int v = v0; v < v0 + nv; ++v) {
+    struct General {
+      ColumnMapF c;
+      float zd;
+    };
+    auto set_up = [&](const double* __restrict__ P) __attribute__((always_inline)) {
+      if constexpr (F == kConeZinv) {
+        return column_map_z_bp(P, ix, iy, iz0);
+      } else {
+        const float zd = (float)P[2];
+        return General{column_map_fp<F == kConeQuadratic>(P, ix, iy, iz0, 1.0f, zd, (float)P[6], (float)P[10]), zd};
+      }
+    };
+    decltype(set_up(proj)) col;   // ZP > 1: formed one view ahead
+    if (ZP > 1 && nv > 0) col = set_up(sP[0]);
+    // view v; ZP > 1: `odd` is the parity of v - v0, and stg[odd] is free for view v + 2 while
+    // stg[odd ^ 1] holds view v + 1
+    auto one_view = [&](int v, auto odd) __attribute__((always_inline)) {
       const int buf = (v - v0) & 1;
       Box nxt{0, 0, 0, 0};
+      constexpr int kOdd = kDepth == 1 ? 0 : decltype(odd)::value;
       const bool more = v + 1 < v0 + nv;
-      if (more) {
-        nxt = box_of(buf ^ 1);
-        load_stage(v + 1, nxt);
+      auto col_next = col;
+      if constexpr (ZP == 1) {
+        if (more) {
+          nxt = box_of(buf ^ 1);
+          load_stage(v + 1, nxt, stg[0]);
+        }
+        if (v + 2 < v0 + nv && wave == ((v - v0) & 3)) publish(v + 2, buf);
+      } else {
+        const int k = v - v0;
+        // past the last view its loads are repeated: with no branch around them the waits
+        // count them, and a store waits for its own view's loads alone
+        nxt = box_of(min(k + 2, nv - 1));
+        load_stage(v0 + min(k + 2, nv - 1), nxt, stg[kOdd]);
+        if (k % kAhead == 0 && k + kAhead < nv) set_out(k + kAhead);
+        col_next = set_up(sP[min(k + 1, nv - 1) & (kRing - 1)]);
       }
-      if (v + 2 < v0 + nv && wave == ((v - v0) & 3)) publish(v + 2, buf);
       const float* t = tile[buf];
       // Tap indices of voxels inside the volume need no clamping: every voxel of the
       // block's box [bx0, bx1] x [by0, by1] x [bz0, bz1] projects inside the convex
@@ -343,26 +439,28 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
       // allocation they return 0, inside it any value), and the results of those
       // lanes and slices are never written (the guards at the end).
       if constexpr (F == kConeZinv) {
-        const ColumnMapZ c = column_map_z(proj + 12 * v, ix, iy, iz0);
+        if constexpr (ZP == 1) col = set_up(proj + 12 * v);
+        const ColumnMapZB& c = col;
         const float* tc = t + (c.i - cur.i_lo);
         // row index = bits(round(w - 1/2) + 1.5 * 2^23) - bias, in tile rows
         const unsigned jbias = kRoundMagicBits - (unsigned)(c.jv0 - cur.j_lo);
 #pragma unroll
-        for (int z = 0; z < kZC; ++z) {
-          const float wm = z == 0 ? c.w0m : fmaf((float)z, c.dw, c.w0m);
+        for (int u = 0; u < kZ; ++u) {
+          const int z = zs + u;
+          const float wm = z == 0 ? c.w0m : z == 1 ? c.w1 : fmaf((float)z, c.dw, c.w0m);
           const float yw = wm + kRoundMagic;
           const float fw = (wm - (yw - kRoundMagic)) + 0.5f;
           const float* r0 = tc + (__float_as_uint(yw) - jbias) * kLP;
           const float a00 = r0[0], a01 = r0[1], a10 = r0[kLP], a11 = r0[kLP + 1];
           const float top = fmaf(c.fu, a01 - a00, a00), bot = fmaf(c.fu, a11 - a10, a10);
-          acc[z] = fmaf(c.r2, fmaf(fw, bot - top, top), acc[z]);
-          if ((z & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+          acc[u] = fmaf(c.r2, fmaf(fw, bot - top, top), acc[u]);
+          if ((u & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
       } else {
         // numerators about iu0 + 1/2, jv0 + 1/2: n r = u - iu0 - 1/2 (and likewise v)
-        const float zd = (float)proj[12 * v + 2];
-        const ColumnMapF c = column_map_fp<F == kConeQuadratic>(proj + 12 * v, ix, iy, iz0, 1.0f, zd,
-                                                                (float)proj[12 * v + 6], (float)proj[12 * v + 10]);
+        if constexpr (ZP == 1) col = set_up(proj + 12 * v);
+        const ColumnMapF& c = col.c;
+        const float zd = col.zd;
         const int oi = c.iu0 - cur.i_lo, oj = c.jv0 - cur.j_lo;
         // kConeQuadratic (den moves by at most 5e-4 of itself per voxel step): 1/den
         // along the column is its quadratic Taylor polynomial about the column's middle
@@ -373,7 +471,8 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
         r0 = fmaf(r0, fmaf(-dc, r0, 1.0f), r0);
         const float r1 = -r0 * r0 * zd, r2 = -r1 * r0 * zd;   // 1/den = r0 + r1 (z - zc) + r2 (z - zc)^2
 #pragma unroll
-        for (int z = 0; z < kZC; ++z) {
+        for (int u = 0; u < kZ; ++u) {
+          const int z = zs + u;
           const float tz = (float)z - zc;
           const float r = F == kConeQuadratic ? fmaf(tz, r1, fmaf(tz * tz, r2, r0))
                           : z == 0            ? r0
@@ -390,20 +489,37 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
           const int q = j * kLP + i;
           const float a00 = t[q], a01 = t[q + 1], a10 = t[q + kLP], a11 = t[q + kLP + 1];
           const float top = fmaf(fu, a01 - a00, a00), bot = fmaf(fu, a11 - a10, a10);
-          acc[z] = fmaf(r * r, fmaf(fw, bot - top, top), acc[z]);
+          acc[u] = fmaf(r * r, fmaf(fw, bot - top, top), acc[u]);
           // Finish every two voxels before the next pair's reads: an empty asm that
           // takes the accumulator as an operand keeps the compiler from sinking the
           // math below later reads (it would hoist all eight voxels' reads and hold
           // their values), so the kernel fits 80 registers and three workgroups per CU
-          if ((z & 1) == 1) {
-            asm volatile("" : "+v"(acc[z]));
+          if ((u & 1) == 1) {
+            asm volatile("" : "+v"(acc[u]));
             __builtin_amdgcn_sched_barrier(0);
           }
         }
       }
-      if (more) store_stage(buf ^ 1);
+      if constexpr (kDepth == 1) {
+        if (more) store_stage(buf ^ 1, stg[0]);
+        cur = nxt;
+      } else {
+        store_stage(buf ^ 1, stg[kOdd ^ 1]);   // after the last view: a buffer no one reads
+        cur = nx1;
+        nx1 = nxt;
+        col = col_next;
+      }
       __syncthreads();
-      cur = nxt;
+    };
+    if constexpr (kDepth == 1) {
+      for (int v = v0; v < v0 + nv; ++v) one_view(v, std::integral_constant<int, 0>{});
+    } else {
+      int v = v0;
+      for (; v + 1 < v0 + nv; v += 2) {
+        one_view(v, std::integral_constant<int, 0>{});
+        one_view(v + 1, std::integral_constant<int, 1>{});
+      }
+      if (v < v0 + nv) one_view(v, std::integral_constant<int, 0>{});
     }
     };
     if constexpr (FORM == kConeMixed) {
@@ -417,11 +533,11 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
   }
   if (ix >= g.nx || iy >= g.ny) return;
 #pragma unroll
-  for (int z = 0; z < kZC; ++z) {
-    const int iz = iz0 + z;
+  for (int u = 0; u < kZ; ++u) {
+    const int iz = iz0 + zs + u;
     if (iz < g.nz) {
       float* o = f + ((size_t)iz * g.ny + iy) * g.nx + ix;
-      float val = acc_in ? *o + acc[z] : acc[z];
+      float val = acc_in ? *o + acc[u] : acc[u];
       *o = relu ? fmaxf(val, 0.f) : val;
     }
   }
@@ -903,15 +1019,24 @@ static hipError_t launch_cone_bp_run(const Plan& p, const void* gF, dc_dtype tF,
                                      int nv, int s_lo, int s_hi, int nzb, int form, hipStream_t s) {
   const int BYr = p.shape.bp_by;
   dim3 grid((p.kg.nx + kBX - 1) / kBX, (p.kg.ny + BYr - 1) / BYr, nzb * (s_hi - s_lo + 1));
+  // Up to 64 blocks leave most of the 256 CUs idle, and each waits on one view's fetch after
+  // another: 8 threads per column segment up to 32 blocks, 4 up to 64 (a 32^3 volume from 90
+  // views 96 -> 48 us, 48^3 97 -> 50, 64^3 from 120 views 140 -> 75; at 216 blocks, 96^3, the
+  // set-up that the threads repeat costs more than the CUs it fills: 143 -> 211)
+  const size_t blocks = (size_t)grid.x * grid.y * grid.z;
+  const int split = BYr != 32 || p.bp_stage == 0 || blocks > 64 ? 1 : blocks > 32 ? 4 : 8;
+  grid.y = (p.kg.ny + BYr / split - 1) / (BYr / split);
   return by_dtype(tF, [&](auto t) {
     using T = decltype(t);
-#define DC_BP1(ST, PI, Z, BY)                                                                                    \
-  hipLaunchKernelGGL((k_cone_bp<T, ST, PI, Z, BY>), grid, dim3(kBX, BY), 0, s, (const T*)gF, f, p.kg, p.d_proj,  \
+#define DC_BP1(ST, PI, Z, BY, ZP)                                                                                    \
+  hipLaunchKernelGGL((k_cone_bp<T, ST, PI, Z, BY, ZP>), grid, dim3(kBX, BY), 0, s, (const T*)gF, f, p.kg, p.d_proj,  \
                      acc, relu, v0, nv, p.d_first, s_lo, nzb, p.d_form)
-#define DC_BP(ST, PI, Z)                   \
-  do {                                     \
-    if (BYr == 16) DC_BP1(ST, PI, Z, 16);  \
-    else DC_BP1(ST, PI, Z, 32);            \
+#define DC_BP(ST, PI, Z)                                                    \
+  do {                                                                      \
+    if (BYr == 16) DC_BP1(ST, PI, Z, 16, 1);                                \
+    else if (ST > 0 && split == 8) DC_BP1(ST, PI, Z, 32, (ST > 0 ? 8 : 1)); \
+    else if (ST > 0 && split == 4) DC_BP1(ST, PI, Z, 32, (ST > 0 ? 4 : 1)); \
+    else DC_BP1(ST, PI, Z, 32, 1);                                          \
   } while (0)
 #define DC_BP_FORMS(ST, PI)                                        \
   switch (form) {                                                  \

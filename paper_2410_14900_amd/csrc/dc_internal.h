@@ -180,9 +180,10 @@ hipError_t launch_zero_u32(unsigned* p, int n, hipStream_t s);
 hipError_t launch_splat(const Plan& p, const void* img, dc_dtype t_in, bool wcos, float scale,
                         void* out, dc_dtype t_out, int v0, int nv, hipStream_t s, unsigned* vmax_words = nullptr);
 // the same stage in its gather form, for plans whose geometry takes it (p.d_splat_ws);
-// vmax: the nv views' largest magnitudes (float bits)
+// vmax: words for the nv views' largest magnitudes (float bits): zero for the exact form, which
+// takes them itself, and formed for the other
 hipError_t launch_splat_shear(const Plan& p, const void* img, dc_dtype t_in, bool wcos, float scale, void* out,
-                              dc_dtype t_out, int v0, int nv, bool exact, hipStream_t s, const unsigned* vmax);
+                              dc_dtype t_out, int v0, int nv, bool exact, hipStream_t s, unsigned* vmax);
 size_t splat_shear_workspace(const Plan& p);
 // The allocation-free splat's static scratch (radon2d.hip): kNoAllocViews words per
 // GPU; *out = its address on `device`, which must be current (looked up once per device).

@@ -274,9 +274,13 @@ __global__ __launch_bounds__(512) void k_splat(const Tin* __restrict__ img, Tout
 // Tile: TX x 64 pixels (TX = 32 or 64, the plan's knob; TX 8 threads); angles
 // per chunk kc <= kInterpMaxKC (knob, at run time).
 static constexpr int kTY = 64;
-static constexpr int kTPX = kTY / 8;   // pixels per thread (rows 8 apart)
+static constexpr int kTPX = kTY / 8;   // pixel rows of a thread (8 apart)
+static constexpr int kSplitHP = 2;     // of a split tile's workgroups
 
-template <typename Tin, typename Tout, bool WCOS, bool LOCAL, int TX>
+// HP: pixels per thread.  A tile's 8 / HP workgroups stage the same windows (the arithmetic of
+// every pixel is the tile's, whichever workgroup forms it); HP = 2 is for calls whose tiles
+// are too few to fill the chip.
+template <typename Tin, typename Tout, bool WCOS, bool LOCAL, int TX, int HP>
 __global__ __launch_bounds__(TX * 8) void k_interp(const Tin* __restrict__ rows, Tout* __restrict__ out, KGrid g,
                                                    const double* __restrict__ angd,
                                                    const float4* __restrict__ viewf, float scale, int v0, int nv,
@@ -291,15 +295,16 @@ __global__ __launch_bounds__(TX * 8) void k_interp(const Tin* __restrict__ rows,
   const int vl = xcd + 8 * (kb / n_tiles);
   if (vl >= nv) return;
   const int v = v0 + vl;
-  const int tile = kb % n_tiles;
+  constexpr int kParts = kTPX / HP;
+  const int tile = kb % n_tiles / kParts, h0 = HP == kTPX ? 0 : kb % kParts * HP;   // n_tiles counts the parts
   const int tu = tile % tiles_u, tv = tile / tiles_u;
   const int i0 = tu * TX, j0 = tv * kTY;
   const int tx = threadIdx.x & (TX - 1), ty = threadIdx.x / TX;  // ty in [0, 8)
   const int ns = g.n_s;
   const Tin* rv = rows + (size_t)v * g.n_theta * ns;
-  float acc[kTPX];
+  float acc[HP];
 #pragma unroll
-  for (int h = 0; h < kTPX; ++h) acc[h] = 0.f;
+  for (int q = 0; q < HP; ++q) acc[q] = 0.f;
   for (int k0 = 0; k0 < g.n_theta; k0 += kc) {
     // uniform: held in a scalar register, so the angle loop costs no vector instructions
     const int kn = __builtin_amdgcn_readfirstlane(min(kc, g.n_theta - k0));
@@ -324,6 +329,7 @@ __global__ __launch_bounds__(TX * 8) void k_interp(const Tin* __restrict__ rows,
     // (kk, e) advances by (blockDim.x / wl, blockDim.x % wl) with one carry, not a division
     const int dkk = blockDim.x / wl, de = blockDim.x - dkk * wl;
     int kk = threadIdx.x / wl, e = threadIdx.x - kk * wl;
+#pragma unroll(HP < kTPX ? 8 : 1)
     for (int q = threadIdx.x; q < kn * wl; q += blockDim.x) {
       const int m = sW0[kk] + e;
       const Tin* r = rv + (size_t)(k0 + kk) * ns;
@@ -349,12 +355,13 @@ __global__ __launch_bounds__(TX * 8) void k_interp(const Tin* __restrict__ rows,
         const double fl = floor(ud);
         long long u = ((long long)((int)fl + kk * wl) << 32) | (long long)(unsigned)((ud - fl) * 4294967296.0);
         const long long step = sStep8[kk];
+        if (HP < kTPX) u += h0 * step;
 #pragma unroll
-        for (int h = 0; h < kTPX; ++h) {
+        for (int q = 0; q < HP; ++q) {
           const unsigned lo = (unsigned)u;
           const float fr = __uint_as_float((lo >> 9) | 0x3f800000u) - 1.0f;   // fraction, 23 bits
           const float2 pr = win[(int)(u >> 32)];
-          acc[h] += fmaf(fr, pr.y, pr.x);
+          acc[q] += fmaf(fr, pr.y, pr.x);
           u += step;
         }
       }
@@ -370,11 +377,12 @@ __global__ __launch_bounds__(TX * 8) void k_interp(const Tin* __restrict__ rows,
       const float b8 = 8.f * P.y;
       const unsigned nbias = (unsigned)__float_as_int(P.w);   // window slot = bits(th + 1.5 2^23) + nbias
 #pragma unroll
-      for (int h = 0; h < kTPX; ++h) {
+      for (int q = 0; q < HP; ++q) {
+        const int h = h0 + q;
         const float th = h == 0 ? th0 : fmaf((float)h, b8, th0);   // 0 b8 + th0 is not folded
         const float y = th + kRoundMagic;
         const float2 pr = win[__float_as_uint(y) + nbias];
-        acc[h] += fmaf(th, pr.y, pr.x);
+        acc[q] += fmaf(th, pr.y, pr.x);
       }
     }
     __syncthreads();
@@ -383,10 +391,10 @@ __global__ __launch_bounds__(TX * 8) void k_interp(const Tin* __restrict__ rows,
   const int i = i0 + tx;
   Tout* o = out + (size_t)v * g.nu * g.nv;
 #pragma unroll
-  for (int h = 0; h < kTPX; ++h) {
-    const int j = j0 + ty + 8 * h;
+  for (int q = 0; q < HP; ++q) {
+    const int j = j0 + ty + 8 * (h0 + q);
     if (i < g.nu && j < g.nv) {
-      float val = scale * acc[h];
+      float val = scale * acc[q];
       if (WCOS) {
         float xu = (i - g.cu) * g.du, yv = (j - g.cv) * g.dv;
         val *= D * __builtin_amdgcn_rsqf(fmaf(xu, xu, fmaf(yv, yv, D * D)));
@@ -429,8 +437,14 @@ hipError_t launch_splat(const Plan& p, const void* img, dc_dtype t_in, bool wcos
   unsigned* vmax = vmax_words ? vmax_words : p.d_scratch + v0;
   hipError_t e = launch_zero_u32(vmax, nv, s);
   if (e != hipSuccess) return e;
+  // The gather forms where the geometry takes them (6.2 and 3.9 ms against 10.6 for 496 views of
+  // 512^2 at 360 angles): float32 sums for the detector Radon stored in float32, the scattering
+  // form's own integer terms otherwise, so that R and whatever is stored in 16 bits is the same in both.
+  const bool exact = p.d_splat_ws && (wcos || t_out != DC_F32);
   return by_dtype(t_in, [&](auto tin) {
     using Tin = decltype(tin);
+    // the exact gather form takes the maxima while it copies (a pass over the views less)
+    if (exact) return launch_splat_shear(p, img, t_in, wcos, scale, out, t_out, v0, nv, true, s, vmax);
     const int mblocks = std::max(1, std::min(64, p.kg.nv / 8));   // about 8 rows per workgroup
 #define DC_ABSMAX(W, VEC)                                                                                    \
   hipLaunchKernelGGL((k_view_absmax<Tin, W, VEC>), dim3(mblocks, nv), dim3(256), 0, s, (const Tin*)img, vmax, \
@@ -444,11 +458,7 @@ hipError_t launch_splat(const Plan& p, const void* img, dc_dtype t_in, bool wcos
 #undef DC_ABSMAX
     hipError_t e2 = hipGetLastError();
     if (e2 != hipSuccess) return e2;
-    // The gather forms where the geometry takes them (6.3 and 3.9 ms against 10.6 for 496 views of
-    // 512^2 at 360 angles): float32 sums for the detector Radon stored in float32, this form's own
-    // integer terms otherwise, so that R and whatever is stored in 16 bits is the same in both.
-    if (p.d_splat_ws)
-      return launch_splat_shear(p, img, t_in, wcos, scale, out, t_out, v0, nv, wcos || t_out != DC_F32, s, vmax);
+    if (p.d_splat_ws) return launch_splat_shear(p, img, t_in, wcos, scale, out, t_out, v0, nv, false, s, vmax);
     return by_dtype(t_out, [&](auto tout) {
       using Tout = decltype(tout);
 #define DC_SPLAT(W, C)                                                                                         \
@@ -470,20 +480,25 @@ hipError_t launch_interp(const Plan& p, const void* rows, dc_dtype t_in, bool wc
                          dc_dtype t_out, int v0, int nv, hipStream_t s) {
   const int TXr = p.shape.interp_tx, kc = p.shape.interp_kc;
   const int tiles_u = (p.kg.nu + TXr - 1) / TXr, tiles_v = (p.kg.nv + kTY - 1) / kTY;
+  // Four workgroups per tile up to half as many tiles as CUs (90 views of 64^2 at 180 angles
+  // 42 -> 28 us, 30 of 33^2 41 -> 21).  With more, the windows that each of the four stages
+  // cost more than they gain (90 of 96^2, 360 tiles, 59 -> 70 us).
+  const bool split = TXr == 64 && (long long)tiles_u * tiles_v * nv <= 128;
   const size_t lds = (size_t)kc * p.interp_wl * sizeof(float2);
-  const int n_tiles = tiles_u * tiles_v;
+  const int n_tiles = tiles_u * tiles_v * (split ? kTPX / kSplitHP : 1);
   dim3 grid(8 * ((nv + 7) / 8) * n_tiles);
   return by_dtype(t_in, [&](auto tin) {
     using Tin = decltype(tin);
     return by_dtype(t_out, [&](auto tout) {
       using Tout = decltype(tout);
-#define DC_INTERP1(W, L, TX)                                                                                     \
-  hipLaunchKernelGGL((k_interp<Tin, Tout, W, L, TX>), grid, dim3(TX * 8), lds, s, (const Tin*)rows, (Tout*)out,  \
+#define DC_INTERP1(W, L, TX, HP)                                                                                 \
+  hipLaunchKernelGGL((k_interp<Tin, Tout, W, L, TX, HP>), grid, dim3(TX * 8), lds, s, (const Tin*)rows, (Tout*)out,  \
                      p.kg, p.d_ang, (const float4*)p.d_view, scale, v0, nv, p.interp_wl, kc, tiles_u, n_tiles)
 #define DC_INTERP(W, L)                      \
   do {                                       \
-    if (TXr == 32) DC_INTERP1(W, L, 32);     \
-    else DC_INTERP1(W, L, 64);               \
+    if (TXr == 32) DC_INTERP1(W, L, 32, 8);  \
+    else if (split) DC_INTERP1(W, L, 64, kSplitHP); \
+    else DC_INTERP1(W, L, 64, 8);            \
   } while (0)
       const bool local = p.interp_wl > kInterpLocalAbove;
       if (wcos) {

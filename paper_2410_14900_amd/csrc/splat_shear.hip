@@ -61,14 +61,16 @@ struct CopyShape {
 // -------------------------------------------------------------------- copy
 // One 32 x 32 tile of four views: both orders (the column order through LDS) of the weighted
 // pixels w x; for the float form rounded to the view's unit, round(w x S) with
-// S = qmax / (largest |w x| of the view).  The tile grid
+// S = qmax / (largest |w x| of the view); for the exact form, which scales while it sums,
+// the views' largest |w x| are taken here (into vmax, zeroed before).  The tile grid
 // covers kPad pixels past the image on both axes, which are written as zeros.  Bound by
 // its writes (8 bytes for every 4 read).
 template <typename Tin, bool WCOS, bool EXACT>
 __global__ __launch_bounds__(256) void k_splat_copy(const Tin* __restrict__ img, f32x4* __restrict__ ws,
-                                                    const unsigned* __restrict__ vmax, KGrid g, CopyShape cs,
+                                                    unsigned* __restrict__ vmax, KGrid g, CopyShape cs,
                                                     const float4* __restrict__ viewf, int v0, int nv, float qmax) {
   __shared__ f32x4 tile[32][33];
+  __shared__ float tops[4][kVB];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int gv = blockIdx.z * kVB;                   // first view of the group, from v0
   const size_t npix = (size_t)g.nu * g.nv;
@@ -78,12 +80,13 @@ __global__ __launch_bounds__(256) void k_splat_copy(const Tin* __restrict__ img,
 #pragma unroll
   for (int b = 0; b < kVB; ++b) {
     const int vl = min(gv + b, nv - 1);
-    const float vm = __uint_as_float(vmax[vl]);
-    S[b] = !EXACT && vm > 0.f ? qmax / vm : 0.f;
+    const float vm = EXACT ? 0.f : __uint_as_float(vmax[vl]);
+    S[b] = vm > 0.f ? qmax / vm : 0.f;
     D[b] = WCOS ? viewf[v0 + vl].x : 0.f;
   }
   const int i = blockIdx.x * 32 + tx;
   const float xu = (i - g.cu) * g.du;
+  float top[kVB] = {};
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int jl = ty + 8 * q, j = blockIdx.y * 32 + jl;
@@ -96,13 +99,29 @@ __global__ __launch_bounds__(256) void k_splat_copy(const Tin* __restrict__ img,
       // hardware rsqrt: the argument is at least D^2, far from the denormal range
       if (WCOS) p *= D[b] * __builtin_amdgcn_rsqf(fmaf(xu, xu, fmaf(yv, yv, D[b] * D[b])));
       x[b] = EXACT ? p : rintf(p * S[b]);
+      if (EXACT) top[b] = fmaxf(top[b], fabsf(p));
     }
     tile[jl][tx] = x;
     if (i < g.nu + kPad && j < cs.rows[0]) rows[(size_t)j * (g.nu + kPad) + kPad + i] = x;
   }
+  if (EXACT) {
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1)
+#pragma unroll
+      for (int b = 0; b < kVB; ++b) top[b] = fmaxf(top[b], __shfl_xor(top[b], m));
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+      for (int b = 0; b < kVB; ++b) tops[threadIdx.x >> 6][b] = top[b];
+    }
+  }
   // the zero pixels before the first row of each form
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kPad) rows[threadIdx.x] = cols[threadIdx.x] = 0.f;
   __syncthreads();
+  if (EXACT && threadIdx.x < kVB && gv + (int)threadIdx.x < nv) {
+    const int b = threadIdx.x;   // magnitudes order like their bits
+    const float t = fmaxf(fmaxf(tops[0][b], tops[1][b]), fmaxf(tops[2][b], tops[3][b]));
+    if (t > 0.f) atomicMax(vmax + gv + b, __float_as_uint(t));
+  }
   const int j = blockIdx.y * 32 + tx;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -522,9 +541,10 @@ size_t splat_shear_workspace(const Plan& p) {
 }
 
 // `exact`: the integer terms of k_splat (bit-identical); otherwise float32 sums of the
-// pixels rounded to its unit.  vmax: the views' largest magnitudes, already formed.
+// pixels rounded to its unit.  vmax: words of the views' largest magnitudes, zero for the exact form and formed
+// for the other.
 hipError_t launch_splat_shear(const Plan& p, const void* img, dc_dtype t_in, bool wcos, float scale, void* out,
-                              dc_dtype t_out, int v0, int nv, bool exact, hipStream_t s, const unsigned* vmax) {
+                              dc_dtype t_out, int v0, int nv, bool exact, hipStream_t s, unsigned* vmax) {
   const CopyShape cs = copy_shape(p);
   // equal batches of view groups
   const int all = (nv + 3) / 4;
