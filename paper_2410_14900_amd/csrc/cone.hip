@@ -14,7 +14,11 @@
 // detector footprint is staged in LDS (converted to float32 from the storage
 // type) and the taps are LDS reads; the next view's footprint is fetched into
 // registers while the current one is interpolated (double buffering, one barrier
-// per view).  For every view the thread forms its column's projection
+// per view).  Footprints and the parts of a view's map that the block shares are set out
+// in LDS for 64 views at a time.  Bound by vector operations, about 28 per voxel and view, 17 of
+// them the voxel's own: with a footprint per view on one wave's shuffles, the shared parts
+// formed by every column and taps addressed with a 32-bit multiply (a quarter of the rate)
+// they were 34, and 496 views into 256^3 took 5.5 ms instead of 5.2.  For every view the thread forms its column's projection
 // coefficients in float64 relative to an integer detector origin near the
 // column's projection, so the float32 per-voxel coordinates stay small and
 // their rounding far below 1e-5 pixel.
@@ -95,21 +99,39 @@ __device__ __forceinline__ ColumnMapZ column_map_z(const double* __restrict__ P,
   return c;
 }
 
-// The backprojection's column, with every rounding spelled out: its forms (one or several
-// threads per column segment) give the same bits whatever the compiler fuses.  v at the
-// second voxel takes its step unrounded.
+// What the columns of a backprojection block share on a view: the parts of den, num_u and
+// num_v that hold for the block's first z, and their z-steps
+struct alignas(16) BlockView {
+  double den, nu, nv;
+  float zd, zu, zv;
+};
+
+__device__ __forceinline__ BlockView block_view(const double* __restrict__ P, int iz0, bool zinv) {
+  BlockView b;
+  b.den = zinv ? P[3] : fma((double)iz0, P[2], P[3]);
+  b.nu = zinv ? P[7] : fma((double)iz0, P[6], P[7]);
+  b.nv = fma((double)iz0, P[10], P[11]);
+  b.zd = (float)P[2];
+  b.zu = (float)P[6];
+  b.zv = (float)P[10];
+  return b;
+}
+
+// The backprojection's z-invariant column, with every rounding spelled out: its forms (one or
+// several threads per column segment) give the same bits whatever the compiler fuses.  v at
+// the second voxel takes its step unrounded.
 struct ColumnMapZB : ColumnMapZ {
   float w1;         // v - jv0 - 1/2 at the second voxel of the segment
 };
 
-__device__ __forceinline__ ColumnMapZB column_map_z_bp(const double* __restrict__ P, int ix, int iy, int iz0) {
+__device__ __forceinline__ ColumnMapZB column_map_z_bp(const double* __restrict__ P, const BlockView& bv, int ix, int iy) {
 #pragma clang fp contract(off)
-  const double den = fma((double)ix, P[0], fma((double)iy, P[1], P[3]));
-  const double nu = fma((double)ix, P[4], fma((double)iy, P[5], P[7]));
-  const double nv = fma((double)ix, P[8], fma((double)iy, P[9], fma((double)iz0, P[10], P[11])));
+  const double den = fma((double)ix, P[0], fma((double)iy, P[1], bv.den));
+  const double nu = fma((double)ix, P[4], fma((double)iy, P[5], bv.nu));
+  const double nv = fma((double)ix, P[8], fma((double)iy, P[9], bv.nv));
   const float rden = __builtin_amdgcn_rcpf((float)den);
   const int iu0 = (int)floorf((float)nu * rden), jv0 = (int)floorf((float)nv * rden);
-  const float nu0 = (float)fma(-(double)iu0, den, nu), nv0 = (float)fma(-(double)jv0, den, nv), dv = (float)P[10];
+  const float nu0 = (float)fma(-(double)iu0, den, nu), nv0 = (float)fma(-(double)jv0, den, nv);
   const float yu = fmaf(nu0, rden, -0.5f) + kRoundMagic;
   ColumnMapZB c;
   c.fu = nu0 * rden - (yu - kRoundMagic);
@@ -117,8 +139,8 @@ __device__ __forceinline__ ColumnMapZB column_map_z_bp(const double* __restrict_
   c.jv0 = jv0;
   c.r2 = rden * rden;
   c.w0m = fmaf(nv0, rden, -0.5f);
-  c.w1 = fmaf(dv, rden, c.w0m);
-  c.dw = dv * rden;
+  c.w1 = fmaf(bv.zv, rden, c.w0m);
+  c.dw = bv.zv * rden;
   return c;
 }
 
@@ -163,6 +185,33 @@ __device__ __forceinline__ ColumnMapF column_map_fp(const double* __restrict__ P
   return c;
 }
 
+typedef const __attribute__((address_space(3))) float* LdsFloats;
+
+// The same for the backprojection (no quantum: sf = 1)
+template <bool FLOAT_STEPS>
+__device__ __forceinline__ ColumnMapF column_map_bp(const double* __restrict__ P, const BlockView& bv, int ix, int iy) {
+  const double den = fma((double)ix, P[0], fma((double)iy, P[1], bv.den));
+  const double nu = fma((double)ix, P[4], fma((double)iy, P[5], bv.nu));
+  const double nv = fma((double)ix, P[8], fma((double)iy, P[9], bv.nv));
+  const float rden = __builtin_amdgcn_rcpf((float)den);
+  const float yu = fmaf((float)nu, rden, kRoundMagic), yv = fmaf((float)nv, rden, kRoundMagic);
+  const float au = (yu - kRoundMagic) + 0.5f, av = (yv - kRoundMagic) + 0.5f;   // exact
+  ColumnMapF c;
+  c.iu0 = (int)(__float_as_uint(yu) - kRoundMagicBits);
+  c.jv0 = (int)(__float_as_uint(yv) - kRoundMagicBits);
+  c.den = (float)den;
+  c.lu = (float)fma(-(double)au, den, nu);
+  c.lv = (float)fma(-(double)av, den, nv);
+  if (FLOAT_STEPS) {
+    c.ldu = fmaf(-au, bv.zd, bv.zu);
+    c.ldv = fmaf(-av, bv.zd, bv.zv);
+  } else {
+    c.ldu = (float)fma(-(double)au, P[2], P[6]);
+    c.ldv = (float)fma(-(double)av, P[2], P[10]);
+  }
+  return c;
+}
+
 static constexpr int kBufferWord3 = 0x00020000;   // raw buffer resource word 3 on this GPU family
 
 // raw buffer load of one storage element (offsets past the resource read 0)
@@ -184,14 +233,12 @@ __device__ __forceinline__ float tap(const T* __restrict__ img, int i, int j, in
 // Footprint of a voxel block on view v: the projective image of the index box
 // lies in the convex hull of its 8 projected corners, so [floor(min)-1,
 // floor(max)+2] in each detector direction covers every bilinear tap (with a
-// pixel of margin for rounding).  Computed by lanes 0..7 of every wave and
-// combined with shuffles, so each wave knows the box without a barrier.
+// pixel of margin for rounding).  Eight lanes form one view's box (P is theirs) and
+// combine their corners with shuffles.
 struct Box {
   int i_lo, j_lo, w, h;
 };
 
-// EACH: every eight lanes their own view's (P differs between them).
-template <bool EACH = false>
 __device__ __forceinline__ Box block_footprint(const double* __restrict__ P, int bx0, int bx1, int by0, int by1,
                                                int bz0, int bz1) {
   const int lane = threadIdx.x & 63;
@@ -211,12 +258,6 @@ __device__ __forceinline__ Box block_footprint(const double* __restrict__ P, int
     jmin = fminf(jmin, __shfl_xor(jmin, m, 8));
     jmax = fmaxf(jmax, __shfl_xor(jmax, m, 8));
   }
-  if (!EACH) {
-    imin = __shfl(imin, 0);
-    imax = __shfl(imax, 0);
-    jmin = __shfl(jmin, 0);
-    jmax = __shfl(jmax, 0);
-  }
   imin = fmaxf(imin, -1.0e6f);
   imax = fminf(imax, 1.0e6f);
   jmin = fmaxf(jmin, -1.0e6f);
@@ -231,8 +272,8 @@ __device__ __forceinline__ Box block_footprint(const double* __restrict__ P, int
 
 // Staging classes and forms whose kernel is compiled for 6 waves per SIMD (three
 // 512-thread workgroups per CU): the quadratic and reciprocal forms with 4 or 8
-// staged rows per thread, the classes real geometries use (80 registers, a few
-// spilled; 7% faster on C2 than at 4 waves).  The others keep the default.
+// staged rows per thread, the classes real geometries use (80 registers; 7%
+// faster on 256^3 from 496 views than at 4 waves).  The others keep the default.
 template <int STAGE, int FORM>
 inline constexpr bool kBpSixWaves = (FORM == kConeQuadratic || FORM == kConeGeneral) && STAGE > 0 && STAGE <= 8;
 
@@ -339,41 +380,34 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
 #pragma unroll
       for (int s = 0; s < STAGE; ++s) tile[buf][(srow + s * kRowsPerPass) * kLP + scol] = to_f32(stg[s]);
     };
-    // ZP == 1: footprints are computed by one wave per view, two views ahead, and passed
-    // on in a two-slot LDS ring: the box of view v sits in slot (v - v0) & 1 from
-    // the barrier that ends iteration v - 2 until all threads have read it at the
-    // start of iteration v - 1, after which the slot takes the box of view v + 2.
-    // ZP > 1: footprints and projection matrices are set out for 64 views at a time, by all
-    // waves, 64 views ahead (a wave's chain of shuffles would hold up every view's barrier).
-    constexpr int kAhead = 64, kRing = ZP == 1 ? 2 : 2 * kAhead;
+    // Footprints, and what a view's columns share, are set out in LDS for kAhead views at a
+    // time, eight lanes per view, kAhead views ahead: the values of view v sit in slot
+    // (v - v0) % kRing from the barrier that ends iteration v - kAhead at the latest.
+    constexpr int kAhead = kBPThreads / 8, kRing = 2 * kAhead;
     __shared__ int4 sBox[kRing];
-    __shared__ double sP[ZP == 1 ? 1 : kRing][12];
-    const int wave = tid >> 6;
-    auto publish = [&](int v, int slot) {
-      const Box b = block_footprint(proj + 12 * v, bx0, bx1, by0, by1, bz0, bz1);
-      if ((tid & 63) == 0) sBox[slot] = make_int4(b.i_lo, b.j_lo, b.w, b.h);
-    };
-    auto set_out = [&](int k0) {   // views v0 + k0 .. + 63
-      for (int q = tid; q < kAhead * 12; q += kBPThreads) {
-        const int k = k0 + q / 12;
-        if (k < nv) sP[k & (kRing - 1)][q % 12] = proj[12 * (v0 + k) + q % 12];
-      }
+    __shared__ BlockView sView[kRing];
+    __shared__ double sP[ZP == 1 ? 1 : kRing][12];   // ZP > 1: the view's matrix too
+    const bool zinv = FORM == kConeMixed ? forms[smp] == kConeZinv : FORM == kConeZinv;
+    auto set_out = [&](int k0) {   // views v0 + k0 .. + kAhead - 1
       const int k = k0 + tid / 8;
-      const Box b = block_footprint<true>(proj + 12 * (v0 + min(k, nv - 1)), bx0, bx1, by0, by1, bz0, bz1);
-      if (k < nv && (tid & 7) == 0) sBox[k & (kRing - 1)] = make_int4(b.i_lo, b.j_lo, b.w, b.h);
+      const double* P = proj + 12 * (v0 + min(k, nv - 1));
+      const Box b = block_footprint(P, bx0, bx1, by0, by1, bz0, bz1);
+      if (k < nv && (tid & 7) == 0) {
+        sBox[k & (kRing - 1)] = make_int4(b.i_lo, b.j_lo, b.w, b.h);
+        sView[k & (kRing - 1)] = block_view(P, iz0, zinv);
+      }
+      if constexpr (ZP > 1) {
+        if (k < nv)
+          for (int q = tid & 7; q < 12; q += 8) sP[k & (kRing - 1)][q] = P[q];
+      }
     };
-    static_assert(ZP == 1 || kBPThreads == 8 * kAhead, "eight lanes per view");
     auto box_of = [&](int k) {
       const int4 b = sBox[k & (kRing - 1)];
       return Box{b.x, b.y, b.z, b.w};
     };
     Box cur{0, 0, 0, 0}, nx1{0, 0, 0, 0};   // boxes of this view and, ZP > 1, the next
     if (nv > 0) {
-      if constexpr (ZP == 1) {
-        if (wave < 2 && wave < nv) publish(v0 + wave, wave);
-      } else {
-        set_out(0);
-      }
+      set_out(0);
       __syncthreads();
       cur = box_of(0);
       load_stage(v0, cur, stg[0]);
@@ -392,16 +426,14 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
       ColumnMapF c;
       float zd;
     };
-    auto set_up = [&](const double* __restrict__ P) __attribute__((always_inline)) {
-      if constexpr (F == kConeZinv) {
-        return column_map_z_bp(P, ix, iy, iz0);
-      } else {
-        const float zd = (float)P[2];
-        return General{column_map_fp<F == kConeQuadratic>(P, ix, iy, iz0, 1.0f, zd, (float)P[6], (float)P[10]), zd};
-      }
+    // the column on view v0 + k with matrix P
+    auto set_up = [&](const double* __restrict__ P, int k) __attribute__((always_inline)) {
+      const BlockView bv = sView[k & (kRing - 1)];
+      if constexpr (F == kConeZinv) return column_map_z_bp(P, bv, ix, iy);
+      else return General{column_map_bp<F == kConeQuadratic>(P, bv, ix, iy), bv.zd};
     };
-    decltype(set_up(proj)) col;   // ZP > 1: formed one view ahead
-    if (ZP > 1 && nv > 0) col = set_up(sP[0]);
+    decltype(set_up(proj, 0)) col;   // ZP > 1: formed one view ahead
+    if (ZP > 1 && nv > 0) col = set_up(sP[0], 0);
     // view v; ZP > 1: `odd` is the parity of v - v0, and stg[odd] is free for view v + 2 while
     // stg[odd ^ 1] holds view v + 1
     auto one_view = [&](int v, auto odd) __attribute__((always_inline)) {
@@ -409,23 +441,33 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
       Box nxt{0, 0, 0, 0};
       constexpr int kOdd = kDepth == 1 ? 0 : decltype(odd)::value;
       const bool more = v + 1 < v0 + nv;
+      const int k = v - v0;
       auto col_next = col;
       if constexpr (ZP == 1) {
         if (more) {
-          nxt = box_of(buf ^ 1);
+          nxt = box_of(k + 1);
           load_stage(v + 1, nxt, stg[0]);
         }
-        if (v + 2 < v0 + nv && wave == ((v - v0) & 3)) publish(v + 2, buf);
+        if (k % kAhead == 0 && k + kAhead < nv) set_out(k + kAhead);
       } else {
-        const int k = v - v0;
         // past the last view its loads are repeated: with no branch around them the waits
         // count them, and a store waits for its own view's loads alone
         nxt = box_of(min(k + 2, nv - 1));
         load_stage(v0 + min(k + 2, nv - 1), nxt, stg[kOdd]);
         if (k % kAhead == 0 && k + kAhead < nv) set_out(k + kAhead);
-        col_next = set_up(sP[min(k + 1, nv - 1) & (kRing - 1)]);
+        col_next = set_up(sP[min(k + 1, nv - 1) & (kRing - 1)], min(k + 1, nv - 1));
       }
-      const float* t = tile[buf];
+      // A tap's address is formed from the bits of the rounded coordinates: their biases
+      // and the tile's place are folded into one base per column, and the row's product is a
+      // 24-bit multiply-add (a 32-bit multiply issues at a quarter of its rate).
+      const unsigned t = (unsigned)(size_t)(LdsFloats)&tile[buf][0];
+      constexpr int kRowBytes = 4 * kLP;
+      auto taps_at = [=](float yu_or_zero, float yw, unsigned base) __attribute__((always_inline)) {
+        unsigned a;   // written out: the compiler would regroup the sum and multiply and add apart
+        asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(a) : "v"(yw), "s"(kRowBytes), "v"(base));
+        return (LdsFloats)(size_t)((__float_as_uint(yu_or_zero) << 2) + a);
+      };
+      constexpr unsigned kRowBias = (kRoundMagicBits & 0xffffffu) * (unsigned)(4 * kLP);
       // Tap indices of voxels inside the volume need no clamping: every voxel of the
       // block's box [bx0, bx1] x [by0, by1] x [bz0, bz1] projects inside the convex
       // hull of its corners' projections, and the box (at most PITCH wide and
@@ -439,18 +481,16 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
       // allocation they return 0, inside it any value), and the results of those
       // lanes and slices are never written (the guards at the end).
       if constexpr (F == kConeZinv) {
-        if constexpr (ZP == 1) col = set_up(proj + 12 * v);
+        if constexpr (ZP == 1) col = set_up(proj + 12 * v, k);
         const ColumnMapZB& c = col;
-        const float* tc = t + (c.i - cur.i_lo);
-        // row index = bits(round(w - 1/2) + 1.5 * 2^23) - bias, in tile rows
-        const unsigned jbias = kRoundMagicBits - (unsigned)(c.jv0 - cur.j_lo);
+        const unsigned base = t + 4u * (unsigned)(__mul24(c.jv0 - cur.j_lo, kLP) + (c.i - cur.i_lo)) - kRowBias;
 #pragma unroll
         for (int u = 0; u < kZ; ++u) {
           const int z = zs + u;
           const float wm = z == 0 ? c.w0m : z == 1 ? c.w1 : fmaf((float)z, c.dw, c.w0m);
           const float yw = wm + kRoundMagic;
           const float fw = (wm - (yw - kRoundMagic)) + 0.5f;
-          const float* r0 = tc + (__float_as_uint(yw) - jbias) * kLP;
+          const LdsFloats r0 = taps_at(0.f, yw, base);
           const float a00 = r0[0], a01 = r0[1], a10 = r0[kLP], a11 = r0[kLP + 1];
           const float top = fmaf(c.fu, a01 - a00, a00), bot = fmaf(c.fu, a11 - a10, a10);
           acc[u] = fmaf(c.r2, fmaf(fw, bot - top, top), acc[u]);
@@ -458,10 +498,11 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
         }
       } else {
         // numerators about iu0 + 1/2, jv0 + 1/2: n r = u - iu0 - 1/2 (and likewise v)
-        if constexpr (ZP == 1) col = set_up(proj + 12 * v);
+        if constexpr (ZP == 1) col = set_up(proj + 12 * v, k);
         const ColumnMapF& c = col.c;
         const float zd = col.zd;
-        const int oi = c.iu0 - cur.i_lo, oj = c.jv0 - cur.j_lo;
+        const unsigned base = t + 4u * (unsigned)(__mul24(c.jv0 - cur.j_lo, kLP) + (c.iu0 - cur.i_lo)) - kRowBias -
+                              (kRoundMagicBits << 2);
         // kConeQuadratic (den moves by at most 5e-4 of itself per voxel step): 1/den
         // along the column is its quadratic Taylor polynomial about the column's middle
         // zc, whose remainder is below (3.5 x 5e-4)^3 of it, far below float rounding
@@ -484,10 +525,8 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
           // inside the box margin), a second fused form the fraction
           const float yu = fmaf(nu, r, kRoundMagic), yw = fmaf(nw, r, kRoundMagic);
           const float fu = fmaf(nu, r, kRoundMagic - yu) + 0.5f, fw = fmaf(nw, r, kRoundMagic - yw) + 0.5f;
-          const int i = oi + (int)(__float_as_uint(yu) - kRoundMagicBits);
-          const int j = oj + (int)(__float_as_uint(yw) - kRoundMagicBits);
-          const int q = j * kLP + i;
-          const float a00 = t[q], a01 = t[q + 1], a10 = t[q + kLP], a11 = t[q + kLP + 1];
+          const LdsFloats q = taps_at(yu, yw, base);
+          const float a00 = q[0], a01 = q[1], a10 = q[kLP], a11 = q[kLP + 1];
           const float top = fmaf(fu, a01 - a00, a00), bot = fmaf(fu, a11 - a10, a10);
           acc[u] = fmaf(r * r, fmaf(fw, bot - top, top), acc[u]);
           // Finish every two voxels before the next pair's reads: an empty asm that
