@@ -41,22 +41,21 @@ FP32_PEAK_TFLOPS = 157.3
 # stages, voxel-view pairs for the cone stages, sinogram bins for the filter
 FLOPS_PER_UNIT = {"weight_radon": 9, "filter": 10, "detector_bp": 9, "cone_bp": 23,
                   "cone_bp_adjoint": 23, "detector_bp_adjoint": 9, "filter_adjoint": 10}
-# LDS bytes per unit the algorithms move: one 8-byte integer atomic per pixel-angle
-# (splat), one 8-byte (c, s) read per pixel-angle (interp), four 4-byte taps per
-# voxel-view (cone BP), two 8-byte atomics per voxel-view (cone transpose), a row
-# staged once per bin (filters, written and read).  Against 128 B per clock per CU
-# (the CDNA3 LDS figure; no CDNA4 one is published), 78.6 TB/s over 256 CUs.
-LDS_BYTES_PER_UNIT = {"weight_radon": 8, "filter": 8, "detector_bp": 8, "cone_bp": 16,
-                      "cone_bp_adjoint": 16, "detector_bp_adjoint": 8, "filter_adjoint": 8}
+# LDS bytes per unit the algorithms move: one 8-byte (c, s) read per pixel-angle
+# (interp), four 4-byte taps per voxel-view (cone BP), two 8-byte atomics per voxel-view
+# (cone transpose), a row staged once per bin (filters, written and read); the gathers of
+# the two Radon stages add three 4-byte sums per 16 rows of a column and angle, and the
+# exact form reads one fraction per pixel-angle of four views.  Against 128 B per clock per
+# CU (the CDNA3 LDS figure; no CDNA4 one is published), 78.6 TB/s over 256 CUs.
+LDS_BYTES_PER_UNIT = {"weight_radon": 1.75, "filter": 8, "detector_bp": 8, "cone_bp": 16,
+                      "cone_bp_adjoint": 16, "detector_bp_adjoint": 0.75, "filter_adjoint": 8}
 LDS_PEAK_TBS = 256 * 128 * 2.4e9 / 1e12
-# The splats issue one 64-bit LDS integer atomic per pixel-angle.  Measured cost of
-# one wave-wide 64-bit atomic per CU on this GPU (microbenchmarks saturating the
-# LDS): 6.4 clocks when the 64 lanes hit consecutive words (the best layout; an
-# earlier probe gave 7.5), 8.1-9.1 for the splat's pattern (lanes on pixel lines two
-# apart), 12-13 when lane pairs share a word.  The splats are reported against the
-# best-layout figure.
-SPLAT_STAGES = ("weight_radon", "detector_bp_adjoint")
-LDS_ATOMIC_FLOOR_CLK = 6.4
+# The Radon gathers are bound by vector instructions: wave instructions per 64
+# pixel-angles from SQ_INSTS_VALU (the exact form: the weighted Radon, and the detector
+# Radon stored in 16 bits; the float form: the detector Radon in float32), against the
+# 1.7 per clock per CU that plain float32 instructions reach.
+VALU_PER_UNIT = {"exact": 6.1, "float": 3.4}
+VALU_PEAK_PER_CLK = 1.7
 
 
 # HBM bytes per call of a stage, from FETCH_SIZE and WRITE_SIZE counter runs of this
@@ -66,16 +65,17 @@ LDS_ATOMIC_FLOOR_CLK = 6.4
 # holding its kernels and launcher, and the shared internal header); after any change
 # to them the roofline reports traffic as null until the counters are taken again.
 STAGE_SOURCES = {
-    "weight_radon": ("radon2d.hip",), "detector_bp": ("radon2d.hip",), "detector_bp_adjoint": ("radon2d.hip",),
+    "weight_radon": ("radon2d.hip", "splat_shear.hip"), "detector_bp": ("radon2d.hip",),
+    "detector_bp_adjoint": ("radon2d.hip", "splat_shear.hip"),
     "filter": ("filter.hip",), "filter_adjoint": ("filter.hip",),
     "cone_bp": ("cone.hip",), "cone_bp_adjoint": ("cone.hip",),
 }
 MEASURED_TRAFFIC = {
     # (stage, storage dtype): (bytes per call, digest of the stage's kernel sources)
-    ("cone_bp_adjoint", "f32"): (3_042_834_369 + 693_060_088,
-                                 "5174c8b6b5b02028f732930dd5b813e223518bf03d14fdef2bc522dfeaf0fabe"),
-    ("weight_radon", "f32"): (1_045_988_176 + 519_000_315,
-                              "e2b0876032bfee707c69dbd5d36f94743ff7bf2b61dcd835f03bfeb6f6467cec"),
+    ("cone_bp_adjoint", "f32"): (3_033_513_029 + 693_060_768,
+                                 "409e56d58fdd5c0fa16ae975f1511e91d1d70958f201afcc9fbb576149fab2ba"),
+    ("weight_radon", "f32"): (4_695_286_409 + 1_690_614_368,
+                              "b9b97c4a4be6e5de3b802f2b8afa820a944e74f46d16ccbded62cddc1886ad5d"),
 }
 
 
@@ -89,12 +89,15 @@ def kernel_sources_digest(stage):
     return h.hexdigest()
 
 
-def atomic_clocks(units, t):
-    """Clocks per wave-wide 64-bit LDS atomic per CU for a splat of `units`
-    pixel-angles (one atomic each) taking t seconds, against the measured floor."""
-    clk = t * 256 * 2.4e9 / (units / 64.0)
-    return {"lds_atomic_clk": round(clk, 2), "lds_atomic_floor_clk": LDS_ATOMIC_FLOOR_CLK,
-            "lds_atomic_frac": round(LDS_ATOMIC_FLOOR_CLK / clk, 3)}
+def valu_issue(stage, store, units, t):
+    """Vector instruction issue of a Radon stage's gather of `units` pixel-angles that
+    takes t seconds (nothing for the other stages)."""
+    if stage not in ("weight_radon", "detector_bp_adjoint"):
+        return {}
+    form = "float" if stage == "detector_bp_adjoint" and store == "f32" else "exact"
+    rate = VALU_PER_UNIT[form] * units / 64.0 / (t * 256 * 2.4e9)
+    return {"valu_per_unit": VALU_PER_UNIT[form], "valu_per_clk_cu": round(rate, 2),
+            "valu_frac": round(rate / VALU_PEAK_PER_CLK, 3)}
 
 
 def log(*a):
@@ -667,8 +670,7 @@ def main():
                               "lds_TB/s": round(units * LDS_BYTES_PER_UNIT[st] / t / 1e12, 2),
                               "lds_frac": round(units * LDS_BYTES_PER_UNIT[st] / t / 1e12 / LDS_PEAK_TBS, 3),
                               "units_per_s": units / t}
-            if st in SPLAT_STAGES:
-                per_kernel[st].update(atomic_clocks(units, t))
+            per_kernel[st].update(valu_issue(st, store, units, t))
         results[store] = dict(ms=ms, kern=kern, per_kernel=per_kernel, work=work, rel_error=tr.rel_error())
         del tr
         torch.cuda.empty_cache()
@@ -720,8 +722,7 @@ def main():
                 "hbm_GBps": round(byts / t / 1e9, 1), "hbm_frac": round(byts / t / 1e9 / HBM_PEAK_GBS, 5),
                 "lds_TBps": round(units * LDS_BYTES_PER_UNIT[dom] / t / 1e12, 2),
                 "lds_frac": round(units * LDS_BYTES_PER_UNIT[dom] / t / 1e12 / LDS_PEAK_TBS, 3)}
-        if dom in SPLAT_STAGES:
-            roof.update(atomic_clocks(units, t))
+        roof.update(valu_issue(dom, main_store, units, t))
     out = {
         "metric": METRIC,
         "value": nvox * V / (r["ms"] * 1e-3),

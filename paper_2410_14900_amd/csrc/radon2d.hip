@@ -15,9 +15,10 @@
 namespace dc {
 
 // ------------------------------------------------------------------ splat
-// One workgroup owns one view and a chunk of <= kc angles whose sinogram rows
-// live in LDS.  Every pixel of the view is read once per chunk.  Pixel p with
-// fractional bin t = m + f deposits x(1-f) on bin m and x f on bin m+1, i.e.
+// The scattering form, for bins narrower than pixels or more than twice as wide (the others
+// take the gathers of splat_shear.hip).  One workgroup owns one view and a chunk of
+// <= kc angles whose sinogram rows live in LDS.  Every pixel of the view is read once
+// per chunk.  Pixel p with fractional bin t = m + f deposits x(1-f) on bin m and x f on bin m+1, i.e.
 //     R(m) = a(m) - b(m) + b(m-1),   a(m) = sum_{m_p = m} x_p,  b(m) = sum_{m_p = m} x_p f_p,
 // so both sums land on the SAME index m_p.  They are accumulated as fixed-point
 // integers packed into one 64-bit word (a + 2^32 b) with a single LDS integer
@@ -437,7 +438,7 @@ hipError_t launch_splat(const Plan& p, const void* img, dc_dtype t_in, bool wcos
   unsigned* vmax = vmax_words ? vmax_words : p.d_scratch + v0;
   hipError_t e = launch_zero_u32(vmax, nv, s);
   if (e != hipSuccess) return e;
-  // The gather forms where the geometry takes them (6.2 and 3.9 ms against 10.6 for 496 views of
+  // The gather forms where the geometry takes them (6.1 and 3.9 ms against 10.6 for 496 views of
   // 512^2 at 360 angles): float32 sums for the detector Radon stored in float32, the scattering
   // form's own integer terms otherwise, so that R and whatever is stored in 16 bits is the same in both.
   const bool exact = p.d_splat_ws && (wcos || t_out != DC_F32);
