@@ -620,23 +620,25 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
 // Tile: TI x kFTJ pixels, TI = 16, 20 or 24 (the plan's knob).
 // kFROWS: rows per enumeration batch; 256 keeps the 20-pixel tile's LDS at 26.7 KB, so
 // six workgroups share a CU (2% faster at C2 than 512 rows at five)
-static constexpr int kFTJ = 64, kFZS = kConeBrick, kFROWS = 256;
+static constexpr int kFTJ = 64, kFZS = kConeBrick, kFThreads = 256;
 static constexpr int kFH = kFTJ + 1;
 
-__device__ __forceinline__ int block_exclusive_scan_256(int v, int* tmp) {
-  // inclusive Hillis-Steele over 256 threads in LDS, returns the exclusive prefix
-  const int t = threadIdx.x;
-  tmp[t] = v;
-  __syncthreads();
-  for (int d = 1; d < 256; d <<= 1) {
-    int add = t >= d ? tmp[t - d] : 0;
-    __syncthreads();
-    tmp[t] += add;
-    __syncthreads();
+// exclusive prefix of v over the workgroup; tmp: a word per wave, free after the next barrier
+// (shuffles and one barrier; a scan through LDS took 18: 496 views of 256^3 6.13 -> 6.06 ms)
+__device__ __forceinline__ int block_exclusive_scan(int v, int* tmp) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int incl = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int add = __shfl_up(incl, d);
+    if (lane >= d) incl += add;
   }
-  int incl = tmp[t];
+  if (lane == 63) tmp[wave] = incl;
   __syncthreads();
-  return incl - v;
+  int before = 0;
+#pragma unroll
+  for (int w = 0; w < kFThreads / 64; ++w) before += w < wave ? tmp[w] : 0;
+  return before + incl - v;
 }
 
 // The gradient (times the ReLU mask when there is one) rewritten in z-bricks,
@@ -707,16 +709,16 @@ __device__ __forceinline__ float pick(const float (&S)[kFV], int w) {
 // workgroups per CU at 80 registers (7.2 ms on C2 against 8.3 at five); the wider
 // tiles' LDS holds them to five or four whatever the register count.
 template <typename Tout, int FORM, int TI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_cone_fp(const float* __restrict__ Gf, Tout* __restrict__ GgF, KGrid g,
+__global__ __launch_bounds__(kFThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_cone_fp(const float* __restrict__ Gf, Tout* __restrict__ GgF, KGrid g,
                                                  const double* __restrict__ proj, const float* __restrict__ rmax2,
                                                  int v0, int nv, int tiles_u, int n_tiles, float qmax,
                                                  const unsigned* __restrict__ gmax_bits,
                                                  const int* __restrict__ first, int s_lo, int s_hi, int ngroups,
                                                  const int* __restrict__ forms) {
   __shared__ double sL[kFV][4][4], sNegInvA[kFV][4];
-  __shared__ int sRow[kFROWS], sXlo[kFROWS], sPre[kFROWS + 1];
-  __shared__ unsigned char sLay[kFROWS];   // z-layer of each listed row (sRow holds its fixed coordinate)
-  __shared__ int sScan[256];
+  __shared__ int sRow[kFThreads], sXlo[kFThreads], sPre[kFThreads + 1];   // the rows of a batch, one per thread
+  __shared__ unsigned char sLay[kFThreads];   // z-layer of each listed row (sRow holds its fixed coordinate)
+  __shared__ int sScan[kFThreads / 64];
   __shared__ int sCount, sNL;
   __shared__ unsigned char sLayerOn[kFMaxLayers];
   __shared__ int sLayer[kFMaxLayers];
@@ -817,12 +819,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 6))) voi
     zstep_u[w] = (float)(P[6] * si);
     zstep_v[w] = (float)(P[10] * si);
   }
-  for (int r0 = 0; r0 < nrows; r0 += kFROWS) {
+  for (int r0 = 0; r0 < nrows; r0 += kFThreads) {
     if (threadIdx.x == 0) sCount = 0;
     __syncthreads();
     // 1. rows of this batch (layer and fixed coordinate) whose interval along the
     // run coordinate may meet one of the frusta (written below for runs along x)
-    for (int r = r0 + threadIdx.x; r < min(nrows, r0 + kFROWS); r += blockDim.x) {
+    const int r = r0 + threadIdx.x;
+    if (r < nrows) {
       const int li = r / nfix, fc = r - li * nfix;
       const int zs = sLayer[li];
       const double zlo = zs * kFZS, zhi = min(g.nz - 1, zs * kFZS + kFZS - 1);
@@ -859,29 +862,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 6))) voi
     }
     __syncthreads();
     const int cnt = sCount;
-    // 2. exclusive prefix of the run lengths (4 entries per thread)
-    int loc[4], sum = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = threadIdx.x * 4 + e;
-      loc[e] = idx < cnt ? sPre[idx] : 0;
-      sum += loc[e];
-    }
-    int run = block_exclusive_scan_256(sum, sScan);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = threadIdx.x * 4 + e;
-      if (idx < cnt) sPre[idx] = run;
-      run += loc[e];
-    }
-    if (threadIdx.x == 255) sPre[cnt] = run;   // total (thread 255 holds the last entries)
+    // 2. exclusive prefix of the run lengths
+    const int len = (int)threadIdx.x < cnt ? sPre[threadIdx.x] : 0;
+    const int run = block_exclusive_scan(len, sScan);
+    if ((int)threadIdx.x < cnt) sPre[threadIdx.x] = run;
+    if (threadIdx.x == kFThreads - 1) sPre[cnt] = run + len;   // the total
     __syncthreads();
     const int total = sPre[cnt];
     // 3. flattened items: (row, x) -> a 16-voxel z-segment, projected on every view.
     // Each wave takes a contiguous quarter of the items, 64 consecutive ones per
     // pass, so a lane's next item lies 64 further on: its row is found once by
     // bisection and then advanced by a short forward scan (rows hold ~15-30 items).
-    const int per_wave = (total + 3) >> 2;
+    constexpr int kWaves = kFThreads / 64;
+    const int per_wave = (total + kWaves - 1) / kWaves;
     const int qa = (threadIdx.x >> 6) * per_wave, qb = min(total, qa + per_wave);
     // the items for one form F (kConeMixed takes the sample's form at run time:
     // one uniform branch per batch, the same arithmetic as the form's own kernel)
@@ -1137,7 +1130,7 @@ hipError_t launch_cone_fp(const Plan& p, const float* Gf, const float* f_relu, v
     if (ng > 0) {
       const dim3 grid(8 * ((n_tiles + 7) / 8) * ng);
 #define DC_FP1(Z, TI)                                                                                        \
-  hipLaunchKernelGGL((k_cone_fp<T, Z, TI>), grid, dim3(256), 0, s, src, (T*)GgF, p.kg, p.d_proj, p.d_rmax2, v0, \
+  hipLaunchKernelGGL((k_cone_fp<T, Z, TI>), grid, dim3(kFThreads), 0, s, src, (T*)GgF, p.kg, p.d_proj, p.d_rmax2, v0, \
                      nv, tiles_u, n_tiles, p.cone_qmax, gmax, p.d_first, s_lo, s_hi, ng, p.d_form)
 #define DC_FP(Z)                                  \
   do {                                            \
