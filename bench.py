@@ -72,9 +72,9 @@ STAGE_SOURCES = {
 }
 MEASURED_TRAFFIC = {
     # (stage, storage dtype): (bytes per call, digest of the stage's kernel sources)
-    ("cone_bp_adjoint", "f32"): (3_033_513_029 + 693_060_768,
-                                 "409e56d58fdd5c0fa16ae975f1511e91d1d70958f201afcc9fbb576149fab2ba"),
-    ("weight_radon", "f32"): (4_695_286_409 + 1_690_614_368,
+    ("cone_bp_adjoint", "f32"): (3_090_529_197 + 693_086_512,
+                                 "01cfd32fff9c0e63751d5dfe20cd3f5361558cf589ccb845f04752610c80ddf2"),
+    ("weight_radon", "f32"): (4_688_446_894 + 1_690_599_936,
                               "b9b97c4a4be6e5de3b802f2b8afa820a944e74f46d16ccbded62cddc1886ad5d"),
 }
 
