@@ -383,12 +383,15 @@ void k_cone_bp(const T* __restrict__ gF, float* __restrict__ f, KGrid g,
     // Footprints, and what a view's columns share, are set out in LDS for kAhead views at a
     // time, eight lanes per view, kAhead views ahead: the values of view v sit in slot
     // (v - v0) % kRing from the barrier that ends iteration v - kAhead at the latest.
-    constexpr int kAhead = kBPThreads / 8, kRing = 2 * kAhead;
+    // Fewer views where the footprints leave little LDS: 8 KB more would cost the deepest
+    // staging classes one of their two workgroups per CU.
+    constexpr int kAhead = ZP == 1 && STAGE > 8 ? 16 : kBPThreads / 8, kRing = 2 * kAhead;
     __shared__ int4 sBox[kRing];
     __shared__ BlockView sView[kRing];
     __shared__ double sP[ZP == 1 ? 1 : kRing][12];   // ZP > 1: the view's matrix too
     const bool zinv = FORM == kConeMixed ? forms[smp] == kConeZinv : FORM == kConeZinv;
     auto set_out = [&](int k0) {   // views v0 + k0 .. + kAhead - 1
+      if (tid >= 8 * kAhead) return;   // whole waves
       const int k = k0 + tid / 8;
       const double* P = proj + 12 * (v0 + min(k, nv - 1));
       const Box b = block_footprint(P, bx0, bx1, by0, by1, bz0, bz1);
