@@ -72,9 +72,9 @@ STAGE_SOURCES = {
 }
 MEASURED_TRAFFIC = {
     # (stage, storage dtype): (bytes per call, digest of the stage's kernel sources)
-    ("cone_bp_adjoint", "f32"): (3_090_529_197 + 693_086_512,
-                                 "01cfd32fff9c0e63751d5dfe20cd3f5361558cf589ccb845f04752610c80ddf2"),
-    ("weight_radon", "f32"): (4_688_446_894 + 1_690_599_936,
+    ("cone_bp_adjoint", "f32"): (3_094_738_906 + 693_083_832,
+                                 "ce2aba7cc86a44f5c5cac9d9caf9d50587afe4da7f93e755d12371c08a80aba9"),
+    ("weight_radon", "f32"): (4_687_652_825 + 1_690_618_224,
                               "b9b97c4a4be6e5de3b802f2b8afa820a944e74f46d16ccbded62cddc1886ad5d"),
 }
 
